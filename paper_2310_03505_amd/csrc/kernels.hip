@@ -37,29 +37,57 @@ __device__ __forceinline__ uint32_t lane_prefix(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Claims this wave's next `pool` rays of a queue of n_in rays.  The queue is
-// split into kCtrSegs segments, each with its own cursor (`cur`, one cursor
-// per kCtrCursorStride words, so on its own cache line): one cursor
-// serialised every wave's claims.  A wave starts at segment `seg` and moves
-// on cyclically once that one is used up; `tries` counts the segments found
-// used up.  On success the rays are [next, end); false once every segment is
-// used up.  Wave-uniform; lane 0 does the atomics.
-__device__ __forceinline__ bool claim_rays(uint32_t* cur, uint32_t n_in, uint32_t pool, uint32_t lane,
-                                           uint32_t& seg, uint32_t& tries, uint32_t& next, uint32_t& end) {
+// How the rays of a queue are handed to the waves of a persistent launch.
+// The first rays are dealt out by wave number, one share of at most 64 rays
+// per wave, with no atomic: a queue of at most one ray per lane of the grid
+// needs no other.  The rays beyond those are claimed dynamically from
+// kCtrSegs segments, each with its own cursor (`cur`, one cursor per
+// kCtrCursorStride words, so on its own cache line): one cursor serialised
+// every wave's claims.  When all rays were claimed, each wave of a short
+// level waited for a claim and then for up to sixteen failing ones before it
+// could end: 400 x 64 rays in a room took 120 us per scan, 78 with the
+// shares; 400 x 1024 rays over the urban block 1.476 ms, 1.432.
+struct Claims {
+  uint32_t* cur;
+  uint32_t first, n_dyn;  // the dynamic part: rays [first, first + n_dyn)
+  uint32_t seg, tries;    // segment of the next claim; segments found used up
+};
+
+// Wave-uniform.  [next, end): this wave's own share.
+__device__ __forceinline__ void claims_init(Claims& q, uint32_t* cur, uint32_t n_in, uint32_t wave, uint32_t n_waves,
+                                            uint32_t& next, uint32_t& end) {
+  const uint32_t share = min((n_in + n_waves - 1u) / n_waves, 64u);
+  next = min(wave * share, n_in);
+  end = min(next + share, n_in);
+  q.cur = cur;
+  q.first = min(n_waves * share, n_in);
+  q.n_dyn = n_in - q.first;
+  q.tries = 0;
+  q.seg = (wave >> 1) & (kCtrSegs - 1u);
+}
+
+// Claims this wave's next `pool` rays of the dynamic part, starting at
+// segment q.seg and moving on cyclically once that one is used up; on success
+// the rays are [next, end), false once every segment is used up.  (Reading
+// all cursors at once to skip used-up segments was slower: city scan 8.42
+// ms, 7.99 ms this way, since at the end of a level every wave reads the
+// sixteen contended lines.)  Wave-uniform; lane 0 does the atomics.
+__device__ __forceinline__ bool claim_rays(Claims& q, uint32_t pool, uint32_t lane, uint32_t& next, uint32_t& end) {
+  if (q.n_dyn == 0u) return false;
 #pragma unroll 1
   for (;;) {
-    const uint32_t s0 = (uint32_t)((uint64_t)n_in * seg / kCtrSegs);
-    const uint32_t s1 = (uint32_t)((uint64_t)n_in * (seg + 1u) / kCtrSegs);
+    const uint32_t s0 = (uint32_t)((uint64_t)q.n_dyn * q.seg / kCtrSegs);
+    const uint32_t s1 = (uint32_t)((uint64_t)q.n_dyn * (q.seg + 1u) / kCtrSegs);
     uint32_t base = 0;
-    if (lane == 0) base = atomicAdd(cur + seg * kCtrCursorStride, pool);
-    base = __shfl(base, 0);
+    if (lane == 0) base = atomicAdd(q.cur + q.seg * kCtrCursorStride, pool);
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
     if (base < s1 - s0) {
-      next = s0 + base;
-      end = min(next + pool, s1);
+      next = q.first + s0 + base;
+      end = min(next + pool, q.first + s1);
       return true;
     }
-    if (++tries >= kCtrSegs) return false;
-    seg = (seg + 1u) & (kCtrSegs - 1u);
+    if (++q.tries >= kCtrSegs) return false;
+    q.seg = (q.seg + 1u) & (kCtrSegs - 1u);
   }
 }
 
@@ -221,6 +249,7 @@ k_trace(LevelArgs A) {
   int32_t* stk = lds_stack + threadIdx.x;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wib = threadIdx.x >> 6;
+  const uint32_t swib = (uint32_t)__builtin_amdgcn_readfirstlane((int)wib);  // wib, known wave-uniform
   const uint32_t wave_base = threadIdx.x - lane;
   const uint32_t n_in = kShadow ? min(A.counters[kCtrShadow], A.shq_cap) : min(A.counters[kCtrCount + A.depth], A.cap);
   const Node4* __restrict__ nodes = A.nodes;
@@ -230,13 +259,12 @@ k_trace(LevelArgs A) {
   const uint32_t tri_batch = min(max(A.tri_batch, 1u), 64u);
 
   bool valid = false, exhausted = false;
-  uint32_t pool_next = 0, pool_end = 0;  // wave-uniform: claimed, not yet started rays
-  // rays are claimed from segment cursors (claim_rays), starting at the
-  // block's segment; closest-hit levels use cursor set `depth`, the
-  // visibility launch the set after the last level's
-  uint32_t seg = blockIdx.x & (kCtrSegs - 1u), seg_tries = 0;
-  uint32_t* const seg_cur =
-      A.counters + kCtrCursor + (kShadow ? kMaxLevels : A.depth) * kCtrSegs * kCtrCursorStride;
+  uint32_t pool_next, pool_end;  // wave-uniform: claimed, not yet started rays
+  // closest-hit levels use cursor set `depth`, the visibility launch the set
+  // after the last level's
+  Claims claims;
+  claims_init(claims, A.counters + kCtrCursor + (kShadow ? kMaxLevels : A.depth) * kCtrSegs * kCtrCursorStride, n_in,
+              blockIdx.x * (kTraceBlock / 64) + swib, gridDim.x * (kTraceBlock / 64), pool_next, pool_end);
   uint32_t ring_head = 0, ring_tail = 0;  // wave-uniform: appended / tested ring entries
   uint32_t ridx = 0, visits = 0, excl = 0xffffffffu, last_pos = 0;
   float ox = 0, oy = 0, oz = 0, dx = 0, dy = 0, dz = 0, best_t = 0;
@@ -271,8 +299,7 @@ k_trace(LevelArgs A) {
     if (!exhausted && (uint32_t)__popcll(idle) >= A.refill) {
 #pragma unroll 1
       for (int pass = 0; pass < 2 && idle; ++pass) {
-        if (pool_next >= pool_end &&
-            !claim_rays(seg_cur, n_in, A.pool, lane, seg, seg_tries, pool_next, pool_end)) {
+        if (pool_next >= pool_end && !claim_rays(claims, A.pool, lane, pool_next, pool_end)) {
           exhausted = true;
           break;
         }
@@ -607,10 +634,13 @@ __global__ void __launch_bounds__(kTraceBlock) k_trace8(LevelArgs A) {
   uint2* gstk = lds_gstack + threadIdx.x;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wib = threadIdx.x >> 6;
+  const uint32_t swib = (uint32_t)__builtin_amdgcn_readfirstlane((int)wib);  // wib, known wave-uniform
   const uint32_t wave_base = threadIdx.x - lane;
   const uint32_t n_in = min(A.counters[kCtrCount + A.depth], A.cap);
-  uint32_t seg = blockIdx.x & (kCtrSegs - 1u), seg_tries = 0;  // claim_rays state
-  uint32_t* const seg_cur = A.counters + kCtrCursor + A.depth * kCtrSegs * kCtrCursorStride;
+  Claims claims;
+  uint32_t pool_next, pool_end;
+  claims_init(claims, A.counters + kCtrCursor + A.depth * kCtrSegs * kCtrCursorStride, n_in,
+              blockIdx.x * (kTraceBlock / 64) + swib, gridDim.x * (kTraceBlock / 64), pool_next, pool_end);
   const Node8* __restrict__ nodes = A.nodes8;
   const float4* __restrict__ tris = A.tris;
   const uint32_t gtid = blockIdx.x * blockDim.x + threadIdx.x;
@@ -619,7 +649,6 @@ __global__ void __launch_bounds__(kTraceBlock) k_trace8(LevelArgs A) {
   const uint32_t tri_batch = min(max(A.tri_batch, 1u), 64u);
 
   bool valid = false, exhausted = false;
-  uint32_t pool_next = 0, pool_end = 0;
   uint32_t ring_head = 0, ring_tail = 0;
   uint32_t ridx = 0, visits = 0, excl = 0xffffffffu, last_pos = 0, oct = 0;
   float ox = 0, oy = 0, oz = 0, dx = 0, dy = 0, dz = 0, best_t = 0;
@@ -637,8 +666,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_trace8(LevelArgs A) {
     if (!exhausted && (uint32_t)__popcll(idle) >= A.refill) {
 #pragma unroll 1
       for (int pass = 0; pass < 2 && idle; ++pass) {
-        if (pool_next >= pool_end &&
-            !claim_rays(seg_cur, n_in, A.pool, lane, seg, seg_tries, pool_next, pool_end)) {
+        if (pool_next >= pool_end && !claim_rays(claims, A.pool, lane, pool_next, pool_end)) {
           exhausted = true;
           break;
         }
@@ -1302,10 +1330,13 @@ __global__ void __launch_bounds__(kTraceBlock) k_scan(LevelArgs A) {
   int32_t* stk = lds_stack + threadIdx.x;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wib = threadIdx.x >> 6;
+  const uint32_t swib = (uint32_t)__builtin_amdgcn_readfirstlane((int)wib);  // wib, known wave-uniform
   const uint32_t wave_base = threadIdx.x - lane;
   const uint32_t n_in = min(A.counters[kCtrCount], A.cap);
-  uint32_t seg = blockIdx.x & (kCtrSegs - 1u), seg_tries = 0;  // claim_rays state (level 0's cursors)
-  uint32_t* const seg_cur = A.counters + kCtrCursor;
+  Claims claims;
+  uint32_t pool_next, pool_end;             // wave-uniform: claimed primaries
+  claims_init(claims, A.counters + kCtrCursor, n_in, blockIdx.x * (kTraceBlock / 64) + swib,
+              gridDim.x * (kTraceBlock / 64), pool_next, pool_end);
   const Node4* __restrict__ nodes = A.nodes;
   const float4* __restrict__ tris = A.tris;
   const uint32_t gtid = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1320,7 +1351,6 @@ __global__ void __launch_bounds__(kTraceBlock) k_scan(LevelArgs A) {
   float4* const hring = pool + (size_t)A.wq_pool * 4u;
 
   bool valid = false, exhausted = false;
-  uint32_t pool_next = 0, pool_end = 0;     // wave-uniform: claimed primaries
   uint32_t ring_head = 0, ring_tail = 0;    // wave-uniform: leaf ring
   uint32_t hit_head = 0, hit_tail = 0;      // wave-uniform: hit ring
   uint32_t pool_n = 0;                      // wave-uniform: children in the pool
@@ -1381,8 +1411,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_scan(LevelArgs A) {
     if (!exhausted && pool_n == 0 && (uint32_t)__popcll(idle) >= A.refill) {
 #pragma unroll 1
       for (int pass = 0; pass < 2 && idle; ++pass) {
-        if (pool_next >= pool_end &&
-            !claim_rays(seg_cur, n_in, A.pool, lane, seg, seg_tries, pool_next, pool_end)) {
+        if (pool_next >= pool_end && !claim_rays(claims, A.pool, lane, pool_next, pool_end)) {
           exhausted = true;
           break;
         }
