@@ -769,13 +769,7 @@ struct Flattener4 {
     }
     invert_empty_slots(ref, qlo, qhi);
     Node4 nd{};
-    uint32_t ebits = eb[0] | (eb[1] << 8) | (eb[2] << 16);
-    float ebf;
-    std::memcpy(&ebf, &ebits, 4);
-    nd.w0 = float4{origin[0], origin[1], origin[2], ebf};
-    nd.w1 = uint4{qlo[0], qhi[0], qlo[1], qhi[1]};
-    nd.w2 = uint4{qlo[2], qhi[2], 0u, 0u};
-    nd.w3 = int4{ref[0], ref[1], ref[2], ref[3]};
+    pack_node4(nd, origin, eb, qlo, qhi, ref);
     out.nodes[idx] = nd;
     // every hit child but the nearest is pushed (leaves too); the deepest
     // inner child adds its own need on top
@@ -1176,7 +1170,7 @@ int32_t host_traverse(const BuiltBvh& b, const float o[3], const float d[3], flo
     }
     const Node4& nd = b.nodes[(size_t)cur];
     float tn[4];
-    uint32_t mask = node4_boxes(nd.w0, nd.w1, nd.w2, nd.w3, rb, best_t, tn);
+    uint32_t mask = node4_boxes(nd.w0, nd.w1, nd.w2, nd.w3, o[0], o[1], o[2], rb, best_t, tn);
     const int32_t ref[4] = {nd.w3.x, nd.w3.y, nd.w3.z, nd.w3.w};
     float key[4];
     int32_t val[4];

@@ -360,10 +360,7 @@ __device__ void write_node(Node4* out, const Kid* kids, int n_kids, float pad) {
   }
   invert_empty_slots(ref, qlo, qhi);
   Node4 nd;
-  nd.w0 = make_float4(origin[0], origin[1], origin[2], __uint_as_float(eb[0] | (eb[1] << 8) | (eb[2] << 16)));
-  nd.w1 = make_uint4(qlo[0], qhi[0], qlo[1], qhi[1]);
-  nd.w2 = make_uint4(qlo[2], qhi[2], 0u, 0u);
-  nd.w3 = make_int4(ref[0], ref[1], ref[2], ref[3]);
+  pack_node4(nd, origin, eb, qlo, qhi, ref);
   *out = nd;
 }
 

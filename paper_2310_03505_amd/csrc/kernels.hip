@@ -37,6 +37,60 @@ __device__ __forceinline__ uint32_t lane_prefix(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Larger and smaller of two ordered (never NaN) float64 values, one
+// instruction each (the library forms first quiet possible signalling NaNs).
+__device__ __forceinline__ double max_f64(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double min_f64(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// Three-input logic operations, one instruction each, which issues at the
+// rate of additions (twice that of selects, shifts and v_and_or / v_or3):
+// b where the bits of m are set and a elsewhere; a | b | c; (a & b) | c.
+__device__ __forceinline__ uint32_t select_bits(uint32_t a, uint32_t b, uint32_t m) {
+  uint32_t r;
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xd8" : "=v"(r) : "v"(a), "v"(b), "v"(m));
+  return r;
+}
+__device__ __forceinline__ uint32_t or3(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xfe" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xea" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+  return r;
+}
+
+// The 64 bytes of node idx as four 16-byte global loads; the address is one
+// 32 x 32 + 64-bit multiply-add.
+typedef uint32_t gu4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void load_node(const Node4* nodes, uint32_t idx, float4& w0, uint4& w1, uint4& w2, int4& w3) {
+  uint64_t at, carry;
+  asm("v_mad_u64_u32 %0, %1, %2, 64, %3" : "=v"(at), "=s"(carry) : "v"(idx), "s"(nodes));
+  const auto* np = reinterpret_cast<const __attribute__((address_space(1))) gu4*>(at);
+  const gu4 a = np[0], b = np[1], c = np[2], d = np[3];
+  w0 = make_float4(__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w));
+  w1 = make_uint4(b.x, b.y, b.z, b.w);
+  w2 = make_uint4(c.x, c.y, c.z, c.w);
+  w3 = make_int4((int)d.x, (int)d.y, (int)d.z, (int)d.w);
+}
+
+// value of lane `from` (a ds_bpermute by lane, all lanes of the wave alive)
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int from) {
+  return (uint32_t)__builtin_amdgcn_ds_bpermute(from << 2, (int)v);
+}
+__device__ __forceinline__ float lane_value(float v, int from) {
+  return __uint_as_float(lane_value(__float_as_uint(v), from));
+}
+
 // How the rays of a queue are handed to the waves of a persistent launch.
 // The first rays are dealt out by wave number, one share of at most 64 rays
 // per wave, with no atomic: a queue of at most one ray per lane of the grid
@@ -223,6 +277,24 @@ __device__ __forceinline__ void normalize3(float& x, float& y, float& z) {
 // leaves changes speed, never the result.  A lane finishes its ray once its
 // stack is empty and the ring has passed its last entry.
 //
+// What bounds it: with many rays per lane the VALU and the vector L1
+// together (per node step of a wave about 165 vector instructions, and four
+// 16-byte loads of 64 different lines, 44 clocks of a compute unit's L1
+// each); with few the longest walks, a chain of node loads and the vector
+// instructions between them.  The step therefore avoids the instructions
+// that only one of a SIMD's two vector pipes takes (compares, selects,
+// minimum and maximum, shifts, conversions: 4.4 clocks per wave, against
+// about 2.8 for additions, FMAs and logic): lane sets are wave masks in
+// scalar registers, conditions are sign bits combined with logic, the far to
+// near sort is ten float64 minima and maxima, and a triangle's three loads
+// go out together, the next triangle's before this one is tested.  City scan
+// (400 x 4096 rays) 7.99 -> 6.90 ms, urban block (400 x 1024) 1.433 -> 1.295,
+// city at 400 x 200 0.607 -> 0.525.  Tried here and not kept: nodes loaded
+// by four lanes together through LDS (fewer L1 lines, but 4 KB of LDS per
+// wave leave 16 waves per CU: 7.86 against 7.02 ms) or by two lanes with a
+// register exchange (6.93 against 6.94), seven waves per SIMD (72 registers,
+// 14-entry stack: 3% slower).
+//
 // kShadow: the same traversal for the air-path visibility rays of the level,
 // each bounded by its distance to the sensor (a triangle at 0 < t <= dist
 // blocks it).  A ray stops walking at its first blocker, and an unblocked
@@ -238,50 +310,58 @@ __device__ __forceinline__ void normalize3(float& x, float& y, float& z) {
 // images and records do not change.  Held to 80 registers, as the plain
 // variant, so that both keep 24 waves per CU resident.
 template <bool kCount, bool kShadow, bool kHelp>
-__global__ void __launch_bounds__(kTraceBlock) __attribute__((amdgpu_waves_per_eu(kHelp ? 6 : 1)))
+__global__ void __launch_bounds__(kTraceBlock) __attribute__((amdgpu_waves_per_eu(6)))
 k_trace(LevelArgs A) {
-  __shared__ int32_t lds_stack[kStack * kTraceBlock];
+  // row 0 of the stack is never written: the top of an empty stack reads it
+  __shared__ int32_t lds_stack[(kStack + 1) * kTraceBlock];
   __shared__ uint32_t lds_leaf[kTraceBlock / 64][kLeafRing];     // leaf reference
   __shared__ uint8_t lds_own[kTraceBlock / 64][kLeafRing];       // lane that appended it
   __shared__ unsigned long long lds_best[kTraceBlock];           // (t bits << 32) | original id
   __shared__ uint32_t lds_help[kHelp ? kTraceBlock : 1];          // helpers walking for each lane's ray
   __shared__ uint8_t lds_pair[kHelp ? kTraceBlock / 64 : 1][64];  // victim lane of each helper rank
-  int32_t* stk = lds_stack + threadIdx.x;
+  int32_t* stk = lds_stack + kTraceBlock + threadIdx.x;
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wib = threadIdx.x >> 6;
-  const uint32_t swib = (uint32_t)__builtin_amdgcn_readfirstlane((int)wib);  // wib, known wave-uniform
-  const uint32_t wave_base = threadIdx.x - lane;
+  const uint32_t wib = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // wave-uniform
+  const uint32_t wave_base = wib * 64u;
   const uint32_t n_in = kShadow ? min(A.counters[kCtrShadow], A.shq_cap) : min(A.counters[kCtrCount + A.depth], A.cap);
   const Node4* __restrict__ nodes = A.nodes;
   const float4* __restrict__ tris = A.tris;
-  const uint32_t gtid = blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t spill_stride = gridDim.x * blockDim.x;
-  const uint32_t tri_batch = min(max(A.tri_batch, 1u), 64u);
+  const uint32_t tri_batch = A.tri_batch;
+  // stack entry s >= kStack of this lane (a workspace row of one entry per lane of the grid)
+  const auto spill_at = [&](int s) {
+    return A.spill + (size_t)(s - kStack) * (gridDim.x * kTraceBlock) + (blockIdx.x * kTraceBlock + threadIdx.x);
+  };
 
-  bool valid = false, exhausted = false;
+  // lanes as wave masks, in scalar registers: those holding a ray, and those
+  // of them with nothing left to visit (stack empty or visit bound reached)
+  uint64_t valid = 0, done = 0;
+  bool exhausted = false;
   uint32_t pool_next, pool_end;  // wave-uniform: claimed, not yet started rays
   // closest-hit levels use cursor set `depth`, the visibility launch the set
   // after the last level's
   Claims claims;
   claims_init(claims, A.counters + kCtrCursor + (kShadow ? kMaxLevels : A.depth) * kCtrSegs * kCtrCursorStride, n_in,
-              blockIdx.x * (kTraceBlock / 64) + swib, gridDim.x * (kTraceBlock / 64), pool_next, pool_end);
+              blockIdx.x * (kTraceBlock / 64) + wib, gridDim.x * (kTraceBlock / 64), pool_next, pool_end);
   uint32_t ring_head = 0, ring_tail = 0;  // wave-uniform: appended / tested ring entries
-  uint32_t ridx = 0, visits = 0, excl = 0xffffffffu, last_pos = 0;
-  float ox = 0, oy = 0, oz = 0, dx = 0, dy = 0, dz = 0, best_t = 0;
-  RayBox rb{};
-  int32_t cur = 0;
+  uint32_t ridx = 0, rounds = 0, excl = 0xffffffffu, last_pos = 0;
+  float ox = 0, oy = 0, oz = 0, dx = 0, dy = 0, dz = 0;
+  // box tests work in scaled distances (ray_scale): 1/d times the scale, the
+  // scale times the slack, and the culling limit, the nearest hit in them
+  float ix = 0, iy = 0, iz = 0, kslack = 0, limit = 0;
+  RaySigns sg{};
+  int32_t cur = kEmpty;
   int sp = 0;
-  bool trav_done = false;  // stack empty (or visit bound reached)
   uint32_t cnt_nodes = 0, cnt_tris = 0, cnt_rays = 0;
   uint64_t cnt_iters = 0, cnt_active = 0, cnt_tail_iters = 0, cnt_tail_active = 0;  // wave-uniform
-  uint32_t cnt_max_visits = 0;
+  uint32_t cnt_visits = 0, cnt_max_visits = 0;
   // tail helping: the lane whose ray this lane walks (itself unless it is a
   // helper), the stack entries below sb handed to helpers
   uint32_t owner = lane;
   int sb = 0;
-  bool helper = false;
+  uint64_t helper = 0;
   uint32_t guard = 0;
   if (kHelp) lds_help[threadIdx.x] = 0u;
+  int32_t top = stk[-kTraceBlock];  // top of the lane's LDS stack
 
   for (;;) {
     // a bound every wave reaches: a level takes far fewer iterations per
@@ -295,20 +375,21 @@ k_trace(LevelArgs A) {
     // ---- refill idle lanes (wave-uniform decision) from the wave's pool of
     // claimed rays; the pool is refilled A.pool rays at a time with one atomic
     // on a segment cursor
-    uint64_t idle = __ballot(!valid);
-    if (!exhausted && (uint32_t)__popcll(idle) >= A.refill) {
+    if (!exhausted && (uint32_t)__popcll(~valid) >= A.refill) {
 #pragma unroll 1
-      for (int pass = 0; pass < 2 && idle; ++pass) {
+      for (int pass = 0; pass < 2 && ~valid; ++pass) {
         if (pool_next >= pool_end && !claim_rays(claims, A.pool, lane, pool_next, pool_end)) {
           exhausted = true;
           break;
         }
+        const uint64_t idle = ~valid;
         const uint32_t take = min((uint32_t)__popcll(idle), pool_end - pool_next);
         const uint32_t rank = lane_prefix(idle);
-        const bool mine = !valid && rank < take;
-        if (mine) {
+        const uint64_t mine = idle & __ballot(rank < take);
+        if (__builtin_amdgcn_inverse_ballot_w64(mine)) {
           const uint32_t my = pool_next + rank;
           float4 a, b;
+          float best_t;
           if constexpr (kShadow) {
             a = A.shq.a[my];
             b = A.shq.b[my];
@@ -330,137 +411,160 @@ k_trace(LevelArgs A) {
           dx = b.x;
           dy = b.y;
           dz = b.z;
+          RayBox rb;
           ray_box_setup(ox, oy, oz, dx, dy, dz, rb);
+          sg = ray_signs(rb);
+          const float k = ray_scale(best_t);
+          ix = rb.ix * k;
+          iy = rb.iy * k;
+          iz = rb.iz * k;
+          kslack = k * kSlabSlack;
+          limit = best_t * kslack;
           ridx = my;
           cur = 0;
           sp = 0;
           sb = 0;
           owner = lane;
-          helper = false;
-          visits = 0;
+          rounds = 0;
           last_pos = ring_head;
-          trav_done = false;
-          valid = true;
-          if (kCount) ++cnt_rays;
+          if (kCount) {
+            ++cnt_rays;
+            cnt_visits = 0;
+          }
         }
+        valid |= mine;
+        done &= ~mine;
+        if (kHelp) helper &= ~mine;
         pool_next += take;
-        idle = __ballot(!valid);
       }
     }
-    const uint64_t live = __ballot(valid);
-    if (live == 0ull) break;  // only once the level is exhausted
+    if (valid == 0ull) break;  // only once the level is exhausted
     if (kCount) {
       ++cnt_iters;
-      cnt_active += (uint64_t)__popcll(live);
+      cnt_active += (uint64_t)__popcll(valid);
       if (exhausted) {
         ++cnt_tail_iters;
-        cnt_tail_active += (uint64_t)__popcll(live);
+        cnt_tail_active += (uint64_t)__popcll(valid);
       }
     }
 
     // ---- node step or triangle phase.  A node step may append up to four
     // leaves per lane, so it runs only while the ring has room for that.
-    const uint64_t walking = __ballot(valid && !trav_done);
+    uint64_t walk = valid & ~done;
     const uint32_t queued = ring_head - ring_tail;
     const bool tri_phase = queued >= tri_batch ||
-                           (queued > 0 && (walking == 0ull || queued + 4u * (uint32_t)__popcll(walking) > kLeafRing));
+                           (queued > 0 && (walk == 0ull || queued + 4u * (uint32_t)__popcll(walk) > kLeafRing));
     if (tri_phase) {
       const uint32_t n = min(queued, 64u);
       const bool take = lane < n;
       const uint32_t pos = (ring_tail + lane) & (kLeafRing - 1u);
       const uint32_t ref = take ? lds_leaf[wib][pos] : 0u;
       const int own = take ? (int)lds_own[wib][pos] : (int)lane;
-      const float rox = __shfl(ox, own), roy = __shfl(oy, own), roz = __shfl(oz, own);
-      const float rdx = __shfl(dx, own), rdy = __shfl(dy, own), rdz = __shfl(dz, own);
-      const uint32_t rexcl = __shfl(excl, own);
+      const float rox = lane_value(ox, own), roy = lane_value(oy, own), roz = lane_value(oz, own);
+      const float rdx = lane_value(dx, own), rdy = lane_value(dy, own), rdz = lane_value(dz, own);
+      const uint32_t rexcl = lane_value(excl, own);
       if (take) {
         unsigned long long cb = lds_best[wave_base + own];
         float tmax = __uint_as_float((uint32_t)(cb >> 32));
         const uint32_t start = leaf_start((int32_t)ref), count = leaf_count((int32_t)ref);
+        // a triangle's three loads go out together, those of the next
+        // triangle before this one is tested
+        const float4* tp = tris + (size_t)start * 3u;
+        float4 ta = tp[0], e1 = tp[1], e2 = tp[2];
 #pragma unroll 1
-        for (uint32_t k = 0; k < count; ++k) {
-          const uint32_t li = start + k;
-          const float4 ta = tris[3 * li + 0];
+        for (uint32_t k = 0;;) {
           const uint32_t orig = __float_as_uint(ta.w);
-          if (orig == rexcl) continue;
-          if (kCount) ++cnt_tris;
-          const float4 e1 = tris[3 * li + 1];
-          const float4 e2 = tris[3 * li + 2];
-          float t;
-          if (ray_tri(rox, roy, roz, rdx, rdy, rdz, ta.x, ta.y, ta.z, e1.x, e1.y, e1.z, e2.x, e2.y, e2.z,
-                      tmax, t)) {
-            const unsigned long long key = ((unsigned long long)__float_as_uint(t) << 32) | orig;
-            if (key < cb) {
-              atomicMin(&lds_best[wave_base + own], key);
-              cb = key;
-              tmax = t;
+          const float4 ua = ta, u1 = e1, u2 = e2;
+          const bool more = ++k < count;
+          if (more) {
+            tp += 3;
+            ta = tp[0];
+            e1 = tp[1];
+            e2 = tp[2];
+          }
+          if (orig != rexcl) {
+            if (kCount) ++cnt_tris;
+            float t;
+            if (ray_tri(rox, roy, roz, rdx, rdy, rdz, ua.x, ua.y, ua.z, u1.x, u1.y, u1.z, u2.x, u2.y, u2.z, tmax,
+                        t)) {
+              const unsigned long long key = ((unsigned long long)__float_as_uint(t) << 32) | orig;
+              if (key < cb) {
+                atomicMin(&lds_best[wave_base + own], key);
+                cb = key;
+                tmax = t;
+              }
             }
           }
+          if (!more) break;
         }
       }
       ring_tail += n;
       __builtin_amdgcn_wave_barrier();
-      if (valid) {
-        const unsigned long long mine = lds_best[wave_base + (kHelp ? owner : lane)];
-        best_t = __uint_as_float((uint32_t)(mine >> 32));
-        // a visibility ray is done at its first blocker
-        if (kShadow && (uint32_t)mine != 0xffffffffu) trav_done = true;
-      }
+      const unsigned long long mine = lds_best[wave_base + (kHelp ? owner : lane)];
+      limit = __uint_as_float((uint32_t)(mine >> 32)) * kslack;
+      // a visibility ray is done at its first blocker
+      if (kShadow) done |= valid & __ballot((uint32_t)mine != 0xffffffffu);
     } else {
       // up to kNodeSteps node steps in a row, each only while the ring has
       // room for four more leaves per walking lane; the refill, triangle and
       // completion checks run once per run of steps
+      // (a ray enters every node at most once; the bound on its rounds of
+      // steps only guards against a malformed tree)
+      done |= walk & __ballot(++rounds > A.n_nodes);
+      walk = valid & ~done;
 #pragma unroll 1
-      for (uint32_t step = 0;;) {
-        // Every lane runs the node step; one without a node to visit (idle,
-        // done, or holding a reference outside the tree) reads the root and
-        // pushes and appends nothing.  Predication instead of a branch keeps
-        // the per-child conditions as wave masks.
-        const bool walk = valid && !trav_done;
-        // top of the LDS stack, read ahead of the decision to pop so the pop
-        // stays an LDS access (entries beyond kStack come from the workspace)
-        const int32_t top = stk[min(max(sp - 1, 0), kStack - 1) * kTraceBlock];
-        // a reference outside the tree (kEmpty: none) takes the next stack
-        // entry; a popped entry still outside it is dropped at the next step
-        if (walk && (uint32_t)cur >= A.n_nodes) {
-          if (sp > sb) {
-            --sp;
-            cur = sp < kStack ? top : A.spill[(size_t)(sp - kStack) * spill_stride + gtid];
-          } else {
-            trav_done = true;
-          }
+      for (uint32_t step = 0; walk;) {
+        // Every lane runs the node step; one without a node to visit (idle or
+        // done) reads the tree's last node and pushes and appends nothing.
+        // A reference outside the tree (kEmpty: none) takes the next stack
+        // entry; `top`, the last entry in LDS, was read at the end of the
+        // step before.
+        const uint64_t need = walk & __ballot((uint32_t)cur >= A.n_nodes);
+        const uint64_t pop = need & __ballot(sp > sb);
+        const uint64_t dry = need & ~pop;
+        const bool popl = __builtin_amdgcn_inverse_ballot_w64(pop);
+        if (pop & __ballot(sp > kStack)) {
+          if (popl && sp > kStack) top = *spill_at(sp - 1);
         }
-        const bool vis = walk & !trav_done & ((uint32_t)cur < A.n_nodes);
-        const float4* np = reinterpret_cast<const float4*>(nodes + (vis ? cur : 0));
-        const float4 w0 = np[0];
-        const uint4 w1 = reinterpret_cast<const uint4*>(np)[1];
-        const uint4 w2 = reinterpret_cast<const uint4*>(np)[2];
-        const int4 w3 = reinterpret_cast<const int4*>(np)[3];
-        if (kCount && vis) ++cnt_nodes;
-        float tn[4];
-        bool hit[4];
-        node4_slabs(w0, w1, w2, rb, best_t, tn, hit);
+        cur = popl ? top : cur;
+        sp -= (int)popl;
+        done |= dry;
+        const uint64_t vis = walk & ~dry;
+        const uint32_t idx = min((uint32_t)cur, A.n_nodes - 1u);
+        float4 w0;
+        uint4 w1, w2;
+        int4 w3;
+        load_node(nodes, idx, w0, w1, w2, w3);
+        if (kCount && __builtin_amdgcn_inverse_ballot_w64(vis)) {
+          ++cnt_nodes;
+          ++cnt_visits;
+        }
+        float tn[4], tf[4];
+        node4_slabs(w0, w1, w2, ox, oy, oz, ix, iy, iz, sg, tn, tf);
+        // The hit tests are differences whose sign bits are combined with
+        // logic operations: subtraction and logic issue at twice the rate of
+        // compares and selects.  A lane that visits nothing has a negative
+        // limit.  Sort keys: the entry distance above the child reference as
+        // one float64, which orders as the distance does (both are >= 0);
+        // children not hit and leaves (references with the sign bit set) get
+        // the sign bit.  Far to near in five compare-exchanges of one minimum
+        // and one maximum each.
+        const float tlim = __builtin_amdgcn_inverse_ballot_w64(vis) ? limit : -1.0f;
         const int32_t lref[4] = {w3.x, w3.y, w3.z, w3.w};
-        // hit inner children far to near, everything else last: 5 compare-exchanges
-        bool lf[4];
-        float key[4];
-        int32_t val[4];
+        uint64_t leaf[4];
+        double key[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          // bitwise, not short-circuit: no branches around the conditions
-          const bool inner = vis & hit[j] & (lref[j] >= 0);
-          lf[j] = vis & hit[j] & (lref[j] < 0);
-          key[j] = inner ? tn[j] : -INFINITY;
-          val[j] = inner ? lref[j] : kEmpty;
+          const uint32_t r = (uint32_t)lref[j];
+          const uint32_t m1 = __float_as_uint(fmaf(tf[j], kSlabSlack, -tn[j])), m2 = __float_as_uint(tlim - tn[j]);
+          leaf[j] = __ballot((int32_t)(r & ~(m1 | m2)) < 0);
+          key[j] = __hiloint2double((int)and_or(or3(m1, m2, r), 0x80000000u, __float_as_uint(tn[j])), lref[j]);
         }
-#define RR_CX(i, j)                     \
-  if (key[j] > key[i]) {                \
-    const float tk = key[i];            \
-    key[i] = key[j];                    \
-    key[j] = tk;                        \
-    const int32_t tv = val[i];          \
-    val[i] = val[j];                    \
-    val[j] = tv;                        \
+#define RR_CX(i, j)                            \
+  {                                            \
+    const double hi = max_f64(key[i], key[j]); \
+    key[j] = min_f64(key[i], key[j]);          \
+    key[i] = hi;                               \
   }
         RR_CX(0, 1) RR_CX(2, 3) RR_CX(0, 2) RR_CX(1, 3) RR_CX(1, 2)
 #undef RR_CX
@@ -471,72 +575,73 @@ k_trace(LevelArgs A) {
         // lane that visits nothing pushes nothing); otherwise entry by entry,
         // deeper ones into the workspace.  The builder bounds the worst-case
         // depth by kStack + kSpill.
-        const bool m1 = key[1] > -INFINITY, m2 = key[2] > -INFINITY, m3 = key[3] > -INFINITY;
-        const int pushes = (int)m1 + (int)m2 + (int)m3;
-        if (sp + 3 <= kStack) {
-          stk[(sp + 0) * kTraceBlock] = val[0];
-          stk[(sp + 1) * kTraceBlock] = val[1];
-          stk[(sp + 2) * kTraceBlock] = val[2];
+        const int32_t v0 = __double2loint(key[0]), v1 = __double2loint(key[1]), v2 = __double2loint(key[2]);
+        const int32_t n0 = __double2hiint(key[0]) >> 31, n1 = __double2hiint(key[1]) >> 31;  // -1: none
+        const int32_t n2 = __double2hiint(key[2]) >> 31, n3 = __double2hiint(key[3]) >> 31;
+        const int pushes = 3 + n1 + n2 + n3;
+        if (__ballot(sp + 3 > kStack) == 0ull) {
+          stk[(sp + 0) * kTraceBlock] = v0;
+          stk[(sp + 1) * kTraceBlock] = v1;
+          stk[(sp + 2) * kTraceBlock] = v2;
           sp += pushes;
+          top = stk[(sp - 1) * kTraceBlock];
         } else {
+          const int32_t val[3] = {v0, v1, v2};
 #pragma unroll
           for (int j = 0; j < 3; ++j) {
             if (j < pushes && sp < kStack + kSpill) {
               if (sp < kStack)
                 stk[sp * kTraceBlock] = val[j];
               else
-                A.spill[(size_t)(sp - kStack) * spill_stride + gtid] = val[j];
+                *spill_at(sp) = val[j];
               ++sp;
             }
           }
+          top = stk[(min(sp, kStack) - 1) * kTraceBlock];
         }
-        if (vis) {
-          cur = m3 ? val[3] : m2 ? val[2] : m1 ? val[1] : val[0];
-          // every node is entered at most once per ray; the bound only guards
-          // against a malformed tree
-          if (++visits > A.n_nodes) trav_done = true;
-        }
+        uint32_t next = select_bits((uint32_t)v0, (uint32_t)kEmpty, (uint32_t)n0);
+        next = select_bits((uint32_t)v1, next, (uint32_t)n1);
+        next = select_bits((uint32_t)v2, next, (uint32_t)n2);
+        cur = (int32_t)select_bits((uint32_t)__double2loint(key[3]), next, (uint32_t)n3);
         // hit leaves into the ring, slot by slot: the lanes with a leaf in slot
-        // j take consecutive entries (one ballot and one prefix count per
-        // slot).  All lanes take part, so the ring head stays the same in
-        // every lane; a lane's leaves all lie before the step's final head.
-        const uint64_t l0 = __ballot(lf[0]), l1 = __ballot(lf[1]);
-        const uint64_t l2 = __ballot(lf[2]), l3 = __ballot(lf[3]);
-        if (l0 | l1 | l2 | l3) {
-          uint32_t p = ring_head;
-          const uint64_t lm[4] = {l0, l1, l2, l3};
+        // j take consecutive entries.  The ring head stays the same in every
+        // lane; a lane's leaves all lie before the step's final head.
+        const uint64_t any = leaf[0] | leaf[1] | leaf[2] | leaf[3];
+        if (any) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            if (lm[j]) {
-              if (lf[j]) {
-                const uint32_t pos = (p + lane_prefix(lm[j])) & (kLeafRing - 1u);
+            if (leaf[j]) {
+              if (__builtin_amdgcn_inverse_ballot_w64(leaf[j])) {
+                const uint32_t pos = (ring_head + lane_prefix(leaf[j])) & (kLeafRing - 1u);
                 lds_leaf[wib][pos] = (uint32_t)lref[j];
                 lds_own[wib][pos] = (uint8_t)(kHelp ? owner : lane);
               }
-              p += (uint32_t)__popcll(lm[j]);
+              ring_head += (uint32_t)__popcll(leaf[j]);
             }
           }
-          if (lf[0] || lf[1] || lf[2] || lf[3]) last_pos = p;
-          ring_head = p;
+          last_pos = __builtin_amdgcn_inverse_ballot_w64(any) ? ring_head : last_pos;
         }
+        walk = valid & ~done;
         if (++step >= kNodeSteps) break;
-        const uint64_t still = __ballot(valid && !trav_done);
-        if (still == 0ull || ring_head - ring_tail + 4u * (uint32_t)__popcll(still) > kLeafRing) break;
+        if (ring_head - ring_tail + 4u * (uint32_t)__popcll(walk) > kLeafRing) break;
       }
     }
     __builtin_amdgcn_wave_barrier();
 
     // ---- rays whose traversal and leaf tests are complete; a helper is done
     // with its subtree, an owner waits until no helper walks for its ray
-    if (kHelp && helper && valid && trav_done && (int32_t)(ring_tail - last_pos) >= 0) {
-      atomicSub(&lds_help[wave_base + owner], 1u);
-      valid = false;
-      helper = false;
+    uint64_t fin = done & valid & __ballot((int32_t)(ring_tail - last_pos) >= 0);
+    if (kHelp) {
+      const uint64_t hfin = fin & helper;
+      if (__builtin_amdgcn_inverse_ballot_w64(hfin)) atomicSub(&lds_help[wave_base + owner], 1u);
+      valid &= ~hfin;
+      helper &= ~hfin;
+      fin &= ~hfin;
+      __builtin_amdgcn_wave_barrier();
+      if (fin) fin &= __ballot(lds_help[threadIdx.x] == 0u);
     }
-    __builtin_amdgcn_wave_barrier();
-    if (valid && trav_done && (int32_t)(ring_tail - last_pos) >= 0 &&
-        (!kHelp || lds_help[threadIdx.x] == 0u)) {
-      if (kCount) cnt_max_visits = max(cnt_max_visits, visits);
+    if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
+      if (kCount) cnt_max_visits = max(cnt_max_visits, cnt_visits);
       const unsigned long long b = lds_best[threadIdx.x];
       if constexpr (kShadow) {
         const bool blocked = (uint32_t)b != 0xffffffffu;
@@ -552,8 +657,8 @@ k_trace(LevelArgs A) {
       } else {
         A.hits[ridx] = make_uint2((uint32_t)(b >> 32), (uint32_t)b);
       }
-      valid = false;
     }
+    valid &= ~fin;
 
     // ---- tail helping: once no rays are left to claim, idle lanes take the
     // bottom entry of a walking lane's stack (two or more entries, all in
@@ -561,24 +666,24 @@ k_trace(LevelArgs A) {
     // the owner's lane, so their hits meet in the owner's minimum
     if (kHelp && exhausted) {
       __builtin_amdgcn_wave_barrier();
-      const bool can_give = valid && !trav_done && sp - sb >= 2 && sp <= kStack;
-      const uint64_t idle_m = __ballot(!valid);
-      const uint64_t give_m = __ballot(can_give);
+      const uint64_t idle_m = ~valid;
+      const uint64_t give_m = valid & ~done & __ballot(sp - sb >= 2 && sp <= kStack);
       const uint32_t k = min((uint32_t)__popcll(idle_m), (uint32_t)__popcll(give_m));
       if (k) {
         const uint32_t rv = lane_prefix(give_m), ri = lane_prefix(idle_m);
-        const bool victim = can_give && rv < k;
+        const bool victim = __builtin_amdgcn_inverse_ballot_w64(give_m) && rv < k;
         if (victim) lds_pair[wib][rv] = (uint8_t)lane;
         __builtin_amdgcn_wave_barrier();
-        const bool takes = !valid && ri < k;
+        const uint64_t takes_m = idle_m & __ballot(ri < k);
+        const bool takes = __builtin_amdgcn_inverse_ballot_w64(takes_m);
         const int v = takes ? (int)lds_pair[wib][ri] : (int)lane;
-        const int vsb = __shfl(sb, v);
-        const uint32_t vown = (uint32_t)__shfl((int)owner, v);
-        const float rox = __shfl(ox, v), roy = __shfl(oy, v), roz = __shfl(oz, v);
-        const float rdx = __shfl(dx, v), rdy = __shfl(dy, v), rdz = __shfl(dz, v);
-        const uint32_t rexcl = (uint32_t)__shfl((int)excl, v);
+        const int vsb = (int)lane_value((uint32_t)sb, v);
+        const uint32_t vown = lane_value(owner, v);
+        const float rox = lane_value(ox, v), roy = lane_value(oy, v), roz = lane_value(oz, v);
+        const float rdx = lane_value(dx, v), rdy = lane_value(dy, v), rdz = lane_value(dz, v);
+        const uint32_t rexcl = lane_value(excl, v);
         if (takes) {
-          cur = lds_stack[vsb * kTraceBlock + wave_base + (uint32_t)v];
+          cur = lds_stack[(vsb + 1) * kTraceBlock + wave_base + (uint32_t)v];
           owner = vown;
           ox = rox;
           oy = roy;
@@ -587,17 +692,26 @@ k_trace(LevelArgs A) {
           dy = rdy;
           dz = rdz;
           excl = rexcl;
+          RayBox rb;
           ray_box_setup(ox, oy, oz, dx, dy, dz, rb);
-          best_t = __uint_as_float((uint32_t)(lds_best[wave_base + vown] >> 32));
+          sg = ray_signs(rb);
+          const float best_t = __uint_as_float((uint32_t)(lds_best[wave_base + vown] >> 32));
+          const float k = ray_scale(best_t);
+          ix = rb.ix * k;
+          iy = rb.iy * k;
+          iz = rb.iz * k;
+          kslack = k * kSlabSlack;
+          limit = best_t * kslack;
           atomicAdd(&lds_help[wave_base + vown], 1u);
           sp = 0;
           sb = 0;
-          visits = 0;
+          rounds = 0;
           last_pos = ring_head;
-          trav_done = false;
-          valid = true;
-          helper = true;
+          if (kCount) cnt_visits = 0;
         }
+        valid |= takes_m;
+        done &= ~takes_m;
+        helper |= takes_m;
         if (victim) ++sb;
       }
     }
@@ -1542,7 +1656,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_scan(LevelArgs A) {
           const int4 w3 = reinterpret_cast<const int4*>(np)[3];
           if (kCount) ++cnt_nodes;
           float tn[4];
-          const uint32_t mask = node4_boxes(w0, w1, w2, w3, rb, best_t, tn);
+          const uint32_t mask = node4_boxes(w0, w1, w2, w3, ox, oy, oz, rb, best_t, tn);
           const int32_t ref[4] = {w3.x, w3.y, w3.z, w3.w};
           float key[4];
           int32_t val[4];

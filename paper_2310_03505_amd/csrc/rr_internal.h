@@ -29,13 +29,16 @@ constexpr int kStack = 16;     // traversal stack entries per lane held in LDS
 constexpr int kSpill = 80;     // further entries per lane in workspace memory
 
 // Four-wide node with quantised child boxes, 64 bytes (four 16-byte loads):
-//   w0 = (origin.x, origin.y, origin.z, exponent bytes ex | ey << 8 | ez << 16)
-//   w1 = (qlo.x[4], qhi.x[4], qlo.y[4], qhi.y[4])   one byte per child
-//   w2 = (qlo.z[4], qhi.z[4], 0, 0)
+//   w0 = (origin.x, origin.y, origin.z, step.x)
+//   w1 = (qlo.x[4], qlo.x[4] ^ qhi.x[4], qlo.y[4], qlo.y[4] ^ qhi.y[4])   one byte per child
+//   w2 = (qlo.z[4], qlo.z[4] ^ qhi.z[4], step.y, step.z)
 //   w3 = child refs: inner node index (< 2^30), kEmpty for no child, or a
 //        leaf: bit 31 | (count - 1) << 27 | first leaf triangle (< 2^27)
-// Child j covers origin + q * 2^(e - 127) on each axis, rounded outward from
-// the padded float box, so decoding never shrinks a box.  A slot without a
+// step: a power of two per axis, as a float (bits in w2).  Child j covers
+// origin + q * step on each axis, rounded outward from the padded float box,
+// so decoding never shrinks a box.  The xor form gives the planes on the
+// ray's near and far side with three logic operations per axis (which issue
+// at twice the rate of selects), and steps stored as floats need no decoding.  A slot without a
 // child (ref kEmpty) holds the inverted box qlo = 255, qhi = 0 on every
 // axis, which no ray interval meets (node4_slabs relies on it).
 struct alignas(64) Node4 {
@@ -212,78 +215,115 @@ RR_HD void ray_box_setup(float ox, float oy, float oz, float dx, float dy, float
   r.oiz = oz * r.iz;
 }
 
-// Entry distances of the four children of a quantised node; returns the mask
-// of children whose box meets [0, tmax].  Per axis the child bounds decode as
-// t = q * (2^e / d) + (origin - o) / d, one fused multiply-add per bound.
-// The near plane of an axis is its low bound when the direction component
-// is positive and its high bound otherwise; fma(q, s, b) is monotone in q,
-// so choosing the byte planes by the sign of 1/d equals taking min / max of
-// both decoded bounds.
-RR_HD uint32_t node4_boxes(const float4& w0, const uint4& w1, const uint4& w2, const int4& w3,
-                           const RayBox& r, float tmax, float tn[4]) {
-  uint32_t eb;
+// Direction signs of a ray as masks: all ones on an axis it travels down.
+struct RaySigns {
+  uint32_t x, y, z;
+};
+RR_HD uint32_t float_bits(float f) {
+  uint32_t u;
+  __builtin_memcpy(&u, &f, 4);
+  return u;
+}
+RR_HD float bits_float(uint32_t u) {
+  float f;
+  __builtin_memcpy(&f, &u, 4);
+  return f;
+}
+RR_HD RaySigns ray_signs(const RayBox& r) {
+  return RaySigns{(uint32_t)((int32_t)float_bits(r.ix) >> 31), (uint32_t)((int32_t)float_bits(r.iy) >> 31),
+                  (uint32_t)((int32_t)float_bits(r.iz) >> 31)};
+}
+
+// Entry (tn) and exit (tf) distances of the four children of a quantised node
+// along the ray, tn cut below at 0 (on the device also above at 1: see
+// ray_scale); the ray meets child j's box within [0, tmax] if
+// tn[j] <= tf[j] * kSlabSlack and tn[j] <= tmax * kSlabSlack.
+// Per axis the child bounds decode as t = q * (step / d) + (origin - o) / d,
+// one fused multiply-add per bound.  The near plane of an axis is its low
+// bound when the direction component is positive and its high bound
+// otherwise; fma(q, s, b) is monotone in q, so choosing the byte planes by the
+// sign of 1/d equals taking min / max of both decoded bounds.  An empty slot
+// holds an inverted box (see Node4), whose entry distance exceeds its exit
+// distance by at least 255 quantisation steps.
+RR_HD float max3_from0(float a, float b, float c) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  eb = __float_as_uint(w0.w);
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3 clamp" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
 #else
-  __builtin_memcpy(&eb, &w0.w, 4);
+  return fmaxf(fmaxf(a, b), fmaxf(c, 0.0f));
 #endif
-  const float sx = pow2_from_byte(eb & 0xffu) * r.ix;
-  const float sy = pow2_from_byte((eb >> 8) & 0xffu) * r.iy;
-  const float sz = pow2_from_byte((eb >> 16) & 0xffu) * r.iz;
-  const float bx = fmaf(w0.x, r.ix, -r.oix);
-  const float by = fmaf(w0.y, r.iy, -r.oiy);
-  const float bz = fmaf(w0.z, r.iz, -r.oiz);
-  const bool px = r.ix >= 0.0f, py = r.iy >= 0.0f, pz = r.iz >= 0.0f;
-  const uint32_t nx = px ? w1.x : w1.y, fx = px ? w1.y : w1.x;
-  const uint32_t ny = py ? w1.z : w1.w, fy = py ? w1.w : w1.z;
-  const uint32_t nz = pz ? w2.x : w2.y, fz = pz ? w2.y : w2.x;
+}
+RR_HD void node4_slabs(const float4& w0, const uint4& w1, const uint4& w2, float ox, float oy, float oz, float ix,
+                       float iy, float iz, const RaySigns& sg, float tn[4], float tf[4]) {
+  const float sx = w0.w * ix;
+  const float sy = bits_float(w2.z) * iy;
+  const float sz = bits_float(w2.w) * iz;
+  const float bx = (w0.x - ox) * ix;
+  const float by = (w0.y - oy) * iy;
+  const float bz = (w0.z - oz) * iz;
+  const uint32_t nx = w1.x ^ (w1.y & sg.x), fx = nx ^ w1.y;
+  const uint32_t ny = w1.z ^ (w1.w & sg.y), fy = ny ^ w1.w;
+  const uint32_t nz = w2.x ^ (w2.y & sg.z), fz = nz ^ w2.y;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float tnx = fmaf(byte_f(nx, j), sx, bx), tfx = fmaf(byte_f(fx, j), sx, bx);
+    const float tny = fmaf(byte_f(ny, j), sy, by), tfy = fmaf(byte_f(fy, j), sy, by);
+    const float tnz = fmaf(byte_f(nz, j), sz, bz), tfz = fmaf(byte_f(fz, j), sz, bz);
+    tn[j] = max3_from0(tnx, tny, tnz);
+    tf[j] = fminf(fminf(tfx, tfy), tfz);
+  }
+}
+
+// Power of two that takes a ray's largest distance tmax below 1/2.  With 1/d
+// scaled by it, node4_slabs works in units of at least twice the ray's
+// length, so cutting an entry distance to [0, 1] costs nothing (it is the
+// clamp of the maximum instruction) and never hides a box: one entered
+// beyond 1 stays beyond the limit, which is at most 1/2.  (Beyond 2^125 the
+// factor stays normal and the cut only visits more; it is at most 1, so 1/d
+// does not overflow.)
+RR_HD float ray_scale(float tmax) {
+  const int32_t e = (int32_t)((float_bits(tmax) >> 23) & 0xffu);
+  const int32_t k = 252 - e;
+  return bits_float((uint32_t)(k < 1 ? 1 : k > 127 ? 127 : k) << 23);
+}
+
+// The slab tests of node4_slabs as a mask of the children met (empty slots
+// left out), in units of the ray's direction.
+RR_HD uint32_t node4_boxes(const float4& w0, const uint4& w1, const uint4& w2, const int4& w3, float ox, float oy,
+                           float oz, const RayBox& r, float tmax, float tn[4]) {
+  float tf[4];
+  const float k = ray_scale(tmax);
+  node4_slabs(w0, w1, w2, ox, oy, oz, r.ix * k, r.iy * k, r.iz * k, ray_signs(r), tn, tf);
+  const float tlim = tmax * k * kSlabSlack;
   const int32_t ref[4] = {w3.x, w3.y, w3.z, w3.w};
   uint32_t mask = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float tnx = fmaf(byte_f(nx, j), sx, bx), tfx = fmaf(byte_f(fx, j), sx, bx);
-    const float tny = fmaf(byte_f(ny, j), sy, by), tfy = fmaf(byte_f(fy, j), sy, by);
-    const float tnz = fmaf(byte_f(nz, j), sz, bz), tfz = fmaf(byte_f(fz, j), sz, bz);
-    const float a = fmaxf(fmaxf(tnx, tny), fmaxf(tnz, 0.0f));
-    const float f = fminf(fminf(tfx, tfy), fminf(tfz, tmax));
-    tn[j] = a;
-    if (a <= f * kSlabSlack && ref[j] != kEmpty) mask |= 1u << j;
-  }
+  for (int j = 0; j < 4; ++j)
+    if (tn[j] <= tf[j] * kSlabSlack && tn[j] <= tlim && ref[j] != kEmpty) mask |= 1u << j;
   return mask;
 }
 
-// The slab tests of node4_boxes without the empty-slot test, for the trace
-// kernel: an empty slot holds an inverted box (see Node4), whose entry
-// distance exceeds its exit distance by at least 255 quantisation steps.
-// hit[j]: child j's box meets [0, tmax]; tn[j]: its entry distance (>= 0).
-RR_HD void node4_slabs(const float4& w0, const uint4& w1, const uint4& w2, const RayBox& r, float tmax,
-                       float tn[4], bool hit[4]) {
-  uint32_t eb;
-#if defined(__HIP_DEVICE_COMPILE__)
-  eb = __float_as_uint(w0.w);
-#else
-  __builtin_memcpy(&eb, &w0.w, 4);
-#endif
-  const float sx = pow2_from_byte(eb & 0xffu) * r.ix;
-  const float sy = pow2_from_byte((eb >> 8) & 0xffu) * r.iy;
-  const float sz = pow2_from_byte((eb >> 16) & 0xffu) * r.iz;
-  const float bx = fmaf(w0.x, r.ix, -r.oix);
-  const float by = fmaf(w0.y, r.iy, -r.oiy);
-  const float bz = fmaf(w0.z, r.iz, -r.oiz);
-  const bool px = r.ix >= 0.0f, py = r.iy >= 0.0f, pz = r.iz >= 0.0f;
-  const uint32_t nx = px ? w1.x : w1.y, fx = px ? w1.y : w1.x;
-  const uint32_t ny = py ? w1.z : w1.w, fy = py ? w1.w : w1.z;
-  const uint32_t nz = pz ? w2.x : w2.y, fz = pz ? w2.y : w2.x;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float tnx = fmaf(byte_f(nx, j), sx, bx), tfx = fmaf(byte_f(fx, j), sx, bx);
-    const float tny = fmaf(byte_f(ny, j), sy, by), tfy = fmaf(byte_f(fy, j), sy, by);
-    const float tnz = fmaf(byte_f(nz, j), sz, bz), tfz = fmaf(byte_f(fz, j), sz, bz);
-    const float a = fmaxf(fmaxf(tnx, tny), fmaxf(tnz, 0.0f));
-    const float f = fminf(fminf(tfx, tfy), fminf(tfz, tmax));
-    tn[j] = a;
-    hit[j] = a <= f * kSlabSlack;
-  }
+// The words of a node from its frame (steps 2^(e - 127)), one byte per child
+// and axis, and child references.
+RR_HD void pack_node4(Node4& nd, const float origin[3], const uint32_t e[3], const uint32_t qlo[3],
+                      const uint32_t qhi[3], const int32_t ref[4]) {
+  nd.w0.x = origin[0];
+  nd.w0.y = origin[1];
+  nd.w0.z = origin[2];
+  nd.w0.w = bits_float(e[0] << 23);
+  nd.w1.x = qlo[0];
+  nd.w1.y = qlo[0] ^ qhi[0];
+  nd.w1.z = qlo[1];
+  nd.w1.w = qlo[1] ^ qhi[1];
+  nd.w2.x = qlo[2];
+  nd.w2.y = qlo[2] ^ qhi[2];
+  nd.w2.z = e[1] << 23;
+  nd.w2.w = e[2] << 23;
+  nd.w3.x = ref[0];
+  nd.w3.y = ref[1];
+  nd.w3.z = ref[2];
+  nd.w3.w = ref[3];
 }
 
 // Eight-wide node, 80 bytes (five 16-byte loads):

@@ -62,3 +62,37 @@ def test_ray_shares_and_claims(R, ctx, rays):
     assert (outs[0]["records"].cpu().numpy()[ok] == ref["records"][ok]).all()
     assert ok.mean() > 0.98 or rays < 100
     assert np.isfinite(outs[0]["image"].cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("size, bin_size, index", [
+    (1.0, 0.044, 0.5),      # a medium thinner than air: the ray's limit exceeds the sensor's range
+    (1.0, 1e30, 2.5),       # limits near the top of float32
+    (1.0, 1e-25, 2.5),      # a range far below any distance: no hit at all
+    (1.5e6, 6.6e4, 2.5),    # coordinates near the largest accepted
+    (2e-3, 8.8e-5, 2.5),    # a scene of centimetres
+])
+def test_box_tests_at_range_extremes(R, ctx, size, bin_size, index):
+    """Box tests work in distances scaled by a power of two per ray; whatever
+    the scale, the closest hits are the oracle's brute-force ones (every
+    non-exempt primary) and equal the eight-wide traversal's, which does not
+    scale."""
+    import torch
+    s = W.tiny_room(n_azimuth=100, rays_per_beam=24, max_bounces=4)
+    s.vertices = (s.vertices * np.float32(size)).astype(np.float32)
+    s.params = dict(s.params, bin_size_m=bin_size)
+    s.materials = [dict(m, n=index) if m["kind"] == W.KIND_DIELECTRIC else m for m in s.materials]
+    outs = []
+    for opts in (dict(), dict(width=8), dict(builder=1)):
+        sc = R.Scene(ctx, s.vertices, s.indices, s.tri_material, **opts)
+        try:
+            outs.append(_records(R, ctx, sc, s, s.params))
+        finally:
+            sc.release()
+    for o in outs[1:]:
+        assert torch.equal(o["records"], outs[0]["records"])
+        assert torch.equal(o["accum"], outs[0]["accum"])
+    ref = oracle.scan_scene(s, records=True, exempt=True)
+    ok = ~ref["exempt"]
+    assert (outs[0]["records"].cpu().numpy()[ok] == ref["records"][ok]).all()
+    hits = (ref["records"] >= 0).sum()
+    assert (hits == 0) == (bin_size < 1e-20)
