@@ -26,12 +26,9 @@ struct GpuBvh {
   int32_t* parent = nullptr;   // [m - 1 + m] parent inner node of inner i, then of position p
   uint32_t* range = nullptr;   // [m - 1][2] first and last sorted position under inner i
   int32_t* head = nullptr;     // [m - 1] four-wide node index of inner i, or -1
-  float* box = nullptr;        // [m - 1 + m][6] boxes of inner nodes, then of single triangles
+  float* box = nullptr;        // [m - 1 + m][6] boxes over the sorted positions (see k_seg), single ones last
   uint32_t* flag = nullptr;    // [nt] head flags during the build
-  uint32_t* depth = nullptr;   // [m - 1] depth of inner i (root 0)
-  uint32_t* order = nullptr;   // [m - 1] inner nodes grouped by depth
-  uint32_t* level = nullptr;   // [2][kMaxTreeDepth] nodes per depth, then scatter cursors
-  std::vector<uint32_t> level_off, level_cnt;  // host copies: where each depth's nodes start
+  uint32_t* order = nullptr;   // [nodes] the inner node each four-wide node stands for
   uint32_t* misc = nullptr;    // scalars (bounds, counts), see bvh_gpu.hip
   void* temp = nullptr;        // sort / scan scratch
   size_t temp_bytes = 0;
@@ -39,6 +36,7 @@ struct GpuBvh {
   uint32_t* ids = nullptr;     // [nt] sort values in
   uint32_t n_nodes = 0, n_leaves = 0, max_depth = 0, max_stack = 0;
   float pad = 0.0f;
+  bool allocated = false;      // every array above is there
 };
 
 // Builds a tree over V (device, nv x 3) / F / M (device copies held by g):
@@ -48,10 +46,10 @@ struct GpuBvh {
 hipError_t gpu_bvh_build(GpuBvh& g, Node4* nodes, float4* tris, float4* aux, hipStream_t st);
 
 // Recomputes triangles, normals, boxes and node frames of the existing tree
-// from g.V (updated by the caller): the leaves, then one launch per depth,
-// deepest first, then the four-wide nodes; stream-ordered, no allocation.
+// from g.V (updated by the caller): the leaves, the boxes over the sorted
+// positions, then the four-wide nodes; stream-ordered, no allocation.
 // (refit = false: the tail of a build, normals already written.)
-hipError_t gpu_bvh_refit(GpuBvh& g, Node4* nodes, float4* tris, float4* aux, hipStream_t st, bool refit = true);
+hipError_t gpu_bvh_refit(const GpuBvh& g, Node4* nodes, float4* tris, float4* aux, hipStream_t st, bool refit = true);
 
 void gpu_bvh_free(GpuBvh& g);
 

@@ -1,13 +1,22 @@
 // bvh_gpu.hip -- linear BVH on the GPU: Morton codes of the triangle
 // centroids, a radix sort, the binary radix tree of Karras ("Maximizing
 // parallelism in the construction of BVHs, octrees, and k-d trees", HPG
-// 2012), bottom-up boxes with one visit counter per inner node, and a
-// collapse of every other level into the four-wide quantised nodes the
-// traversal kernels read.  Every inner node covers a contiguous range of the
-// sorted triangles, so a subtree of at most max_leaf triangles becomes one
-// leaf without copying.  A refit keeps the tree and recomputes triangles,
-// normals, boxes and node frames from moved vertices; a four-wide tree built
-// on the host is refitted the same way, one launch per depth of its nodes.
+// 2012), and a collapse of every other level into the four-wide quantised
+// nodes the traversal kernels read.  Every inner node covers a contiguous
+// range of the sorted triangles, so a subtree of at most max_leaf triangles
+// becomes one leaf without copying, and a node's box is a range query over
+// the sorted triangles' boxes (an implicit binary tree over the positions,
+// three launches to fill for two million triangles).  A refit keeps the tree
+// and recomputes triangles, normals, boxes and node frames from moved
+// vertices; a four-wide tree built on the host is refitted one launch per
+// depth of its nodes.
+//
+// Every kernel here moves a few hundred megabytes at most, so what bounded
+// them was elsewhere: same-address atomics (one per wave and counter: 62,000
+// at about 10 ns each), 33 launches for the boxes, float64 divisions and
+// dynamically indexed arrays in the node frames.  On two million triangles:
+// k_prep 730 -> 65 us, k_heads 723 -> 50, boxes 345 -> 40, k_emit 413 -> 90;
+// a refit's normals and leaves 175 -> 75, its k_emit 251 -> 91.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,7 +37,7 @@ constexpr int kB = 256;
 // misc words: [0..2] centroid minimum and [3..5] maximum (order-preserving
 // encodings), [6] largest coordinate magnitude (float bits, >= 1), [7]
 // hittable triangles, [8] four-wide nodes, [9] leaves, [10] deepest
-// four-wide node, [11] deepest binary inner node
+// four-wide node
 constexpr int kMiscWords = 16;
 
 __device__ __forceinline__ uint32_t fenc(float f) {
@@ -94,57 +103,89 @@ __global__ void k_init_misc(uint32_t* misc, bool refit) {
   misc[i] = i < 3 ? 0xffffffffu : (i == 6 ? __float_as_uint(1.0f) : 0u);
 }
 
-// per triangle: normal record, hittable count, centroid (into `cen`),
-// centroid bounds and the largest coordinate magnitude (block-reduced)
-__global__ void __launch_bounds__(kB) k_prep(GpuBvh g, float4* aux, float4* cen, bool build) {
-  __shared__ uint32_t s_lo[3], s_hi[3], s_mag, s_cnt;
-  if (threadIdx.x < 3) {
-    s_lo[threadIdx.x] = 0xffffffffu;
-    s_hi[threadIdx.x] = 0u;
-  }
-  if (threadIdx.x == 0) {
-    s_mag = __float_as_uint(1.0f);
-    s_cnt = 0;
-  }
+// Kernels that end in one atomic per block and scalar use large blocks, so
+// that 512 of them fill the chip: same-address atomics take about 10 ns each.
+constexpr int kBig = 1024;
+
+// Combines one value per lane over the block (kLanes lanes) with `op`; the
+// result is valid in thread 0.  `buf` holds one word per wave.
+template <int kLanes = kBig, class Op>
+__device__ __forceinline__ uint32_t block_reduce(uint32_t v, uint32_t* buf, Op op) {
+  for (int d = 32; d >= 1; d >>= 1) v = op(v, (uint32_t)__shfl_xor((int)v, d));
   __syncthreads();
-  const uint32_t j = blockIdx.x * kB + threadIdx.x;
-  if (j < g.nt) {
+  if ((threadIdx.x & 63u) == 0) buf[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int w = 1; w < kLanes / 64; ++w) v = op(v, buf[w]);
+  return v;
+}
+__device__ __forceinline__ uint32_t op_min(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__device__ __forceinline__ uint32_t op_max(uint32_t a, uint32_t b) { return a > b ? a : b; }
+__device__ __forceinline__ uint32_t op_add(uint32_t a, uint32_t b) { return a + b; }
+
+__device__ __forceinline__ float tri_magnitude(const float lo[3], const float hi[3], float mag) {
+  for (int k = 0; k < 3; ++k) mag = fmaxf(mag, fmaxf(fabsf(lo[k]), fabsf(hi[k])));
+  return mag;
+}
+
+// Build, per triangle: normal record, hittable count, centroid (into `cen`),
+// centroid bounds and the largest coordinate magnitude.  Each lane keeps its
+// own bounds over its triangles; one atomic per block and scalar at the end.
+__global__ void __launch_bounds__(kBig) k_prep(GpuBvh g, float4* aux, float4* cen) {
+  __shared__ uint32_t buf[kBig / 64];
+  uint32_t blo[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, bhi[3] = {0u, 0u, 0u}, cnt = 0;
+  float mag = 1.0f;
+  for (uint32_t j = blockIdx.x * kBig + threadIdx.x; j < g.nt; j += gridDim.x * kBig) {
     Tri t;
     load_tri(g, j, t);
     aux[j] = aux_of(g, j, t);
-    const bool ok = t.nn > 0.0f;
-    if (ok) {
-      float lo[3], hi[3], mag = 1.0f;
+    if (t.nn > 0.0f) {
+      float lo[3], hi[3], c[3];
       tri_box(t, lo, hi);
-      float c[3];
+      mag = tri_magnitude(lo, hi, mag);
       for (int k = 0; k < 3; ++k) {
         c[k] = 0.5f * (lo[k] + hi[k]);
-        mag = fmaxf(mag, fmaxf(fabsf(lo[k]), fabsf(hi[k])));
+        blo[k] = op_min(blo[k], fenc(c[k]));
+        bhi[k] = op_max(bhi[k], fenc(c[k]));
       }
-      atomicMax(&s_mag, __float_as_uint(mag));  // positive floats order as their bits
-      if (build) {
-        cen[j] = make_float4(c[0], c[1], c[2], 1.0f);
-        for (int k = 0; k < 3; ++k) {
-          atomicMin(&s_lo[k], fenc(c[k]));
-          atomicMax(&s_hi[k], fenc(c[k]));
-        }
-        atomicAdd(&s_cnt, 1u);
-      }
-    } else if (build) {
+      cen[j] = make_float4(c[0], c[1], c[2], 1.0f);
+      ++cnt;
+    } else {
       cen[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    atomicMax(g.misc + 6, s_mag);
-    if (build) {
-      for (int k = 0; k < 3; ++k) {
-        atomicMin(g.misc + k, s_lo[k]);
-        atomicMax(g.misc + 3 + k, s_hi[k]);
-      }
-      atomicAdd(g.misc + 7, s_cnt);
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t lo = block_reduce(blo[k], buf, op_min), hi = block_reduce(bhi[k], buf, op_max);
+    if (threadIdx.x == 0) {
+      atomicMin(g.misc + k, lo);
+      atomicMax(g.misc + 3 + k, hi);
     }
   }
+  // positive floats order as their bits
+  const uint32_t m = block_reduce(__float_as_uint(mag), buf, op_max), n = block_reduce(cnt, buf, op_add);
+  if (threadIdx.x == 0) {
+    atomicMax(g.misc + 6, m);
+    atomicAdd(g.misc + 7, n);
+  }
+}
+
+// Refit of a host-built tree, per triangle: normal record and the largest
+// coordinate magnitude.
+__global__ void __launch_bounds__(kBig) k_normals(GpuBvh g, float4* aux) {
+  __shared__ uint32_t buf[kBig / 64];
+  float mag = 1.0f;
+  for (uint32_t j = blockIdx.x * kBig + threadIdx.x; j < g.nt; j += gridDim.x * kBig) {
+    Tri t;
+    load_tri(g, j, t);
+    aux[j] = aux_of(g, j, t);
+    if (t.nn > 0.0f) {
+      float lo[3], hi[3];
+      tri_box(t, lo, hi);
+      mag = tri_magnitude(lo, hi, mag);
+    }
+  }
+  const uint32_t m = block_reduce(__float_as_uint(mag), buf, op_max);
+  if (threadIdx.x == 0) atomicMax(g.misc + 6, m);
 }
 
 __device__ __forceinline__ uint32_t spread10(uint32_t x) {
@@ -217,106 +258,138 @@ __global__ void __launch_bounds__(kB) k_internal(GpuBvh g) {
   if (i == 0) g.parent[0] = -1;
 }
 
-// per sorted position: the leaf-order triangle and its box
-__global__ void __launch_bounds__(kB) k_leaves(GpuBvh g, float4* tris) {
-  const int m = (int)g.misc[7];
-  const int p = (int)(blockIdx.x * kB + threadIdx.x);
-  if (p >= m) return;
-  const uint32_t orig = g.sorted[p];
-  Tri t;
-  load_tri(g, orig, t);
-  store_tri(tris + 3 * p, orig, t);
-  float lo[3], hi[3];
-  tri_box(t, lo, hi);
-  float* b = g.box + 6u * (uint32_t)((m - 1) + p);
-  for (int k = 0; k < 3; ++k) {
-    b[k] = lo[k];
-    b[3 + k] = hi[k];
+// Per sorted position: the leaf-order triangle and its box.  kRefit: also the
+// normal record of the position's triangle (unhittable ones, sorted last,
+// have no leaf) and the largest coordinate magnitude, so that a refit reads
+// the moved vertices once.
+template <bool kRefit>
+__global__ void __launch_bounds__(kBig) k_leaves(GpuBvh g, float4* tris, float4* aux) {
+  __shared__ uint32_t buf[kBig / 64];
+  const uint32_t m = g.misc[7], n = kRefit ? g.nt : m;
+  float mag = 1.0f;
+  for (uint32_t p = blockIdx.x * kBig + threadIdx.x; p < n; p += gridDim.x * kBig) {
+    const uint32_t orig = g.sorted[p];
+    Tri t;
+    load_tri(g, orig, t);
+    float lo[3], hi[3];
+    tri_box(t, lo, hi);
+    if (kRefit) {
+      aux[orig] = aux_of(g, orig, t);
+      if (t.nn > 0.0f) mag = tri_magnitude(lo, hi, mag);
+    }
+    if (p < m) {
+      store_tri(tris + 3 * (size_t)p, orig, t);
+      float* b = g.box + 6 * (size_t)(m - 1u + p);
+      for (int k = 0; k < 3; ++k) {
+        b[k] = lo[k];
+        b[3 + k] = hi[k];
+      }
+    }
+  }
+  if (kRefit) {
+    const uint32_t top = block_reduce(__float_as_uint(mag), buf, op_max);
+    if (threadIdx.x == 0) atomicMax(g.misc + 6, top);
   }
 }
 
-// boxes of the inner nodes of one depth from their children (one launch per
-// depth, deepest first, so the children are complete without any fence)
-__global__ void __launch_bounds__(kB) k_box_level(GpuBvh g, uint32_t first, uint32_t count) {
-  const uint32_t k = blockIdx.x * kB + threadIdx.x;
-  if (k >= count) return;
-  const int m = (int)g.misc[7];
-  const int node = (int)g.order[first + k];
-  const int l = g.child[2 * node], r = g.child[2 * node + 1];
-  const float* bl = g.box + 6u * (uint32_t)(l >= 0 ? l : (m - 1) + ~l);
-  const float* br = g.box + 6u * (uint32_t)(r >= 0 ? r : (m - 1) + ~r);
-  float* bn = g.box + 6u * (uint32_t)node;
+// Boxes over the sorted positions as an implicit binary tree: node t covers
+// nodes 2t and 2t + 1, position p is node m + p, node t is slot t - 1 of the
+// box array.  One block fills the subtree below root r over kSegLevels levels
+// whose deepest one is level `top` of the tree (levels deeper than that are
+// positions or filled by the launch before); nodes at m or above are
+// positions.
+constexpr int kSegLevels = 9;
+__global__ void __launch_bounds__(kB) k_seg(GpuBvh g, uint32_t root_level, uint32_t levels) {
+  __shared__ float s_box[2][kB][6];
+  const uint32_t m = g.misc[7];
+  const uint32_t r = (1u << root_level) + blockIdx.x;
+  // levels - 1 .. 0 below the root; the deepest one's children are in memory
+  for (int h = (int)levels - 1; h >= 0; --h) {
+    const uint32_t j = threadIdx.x;
+    const uint64_t t = ((uint64_t)r << h) + j;
+    const int cur = h & 1;
+    if (j < (1u << h) && t < m) {
+      float c[2][6];
+      for (int k = 0; k < 2; ++k) {
+        const uint64_t child = 2 * t + (uint64_t)k;
+        const float* b = g.box + 6 * (size_t)(child - 1);
+        const bool here = h < (int)levels - 1 && child < m;  // computed by this block's last round
+        for (int a = 0; a < 6; ++a) c[k][a] = here ? s_box[cur ^ 1][2 * j + k][a] : b[a];
+      }
+      float* o = g.box + 6 * (size_t)(t - 1);
+      for (int a = 0; a < 6; ++a) {
+        const float v = a < 3 ? fminf(c[0][a], c[1][a]) : fmaxf(c[0][a], c[1][a]);
+        s_box[cur][j][a] = v;
+        o[a] = v;
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// box of sorted positions first..last
+__device__ __forceinline__ void range_box(const GpuBvh& g, uint32_t m, uint32_t first, uint32_t last, float lo[3],
+                                          float hi[3]) {
   for (int a = 0; a < 3; ++a) {
-    bn[a] = fminf(bl[a], br[a]);
-    bn[3 + a] = fmaxf(bl[3 + a], br[3 + a]);
+    lo[a] = INFINITY;
+    hi[a] = -INFINITY;
   }
-}
-
-// inner nodes into depth buckets (positions from the host's prefix sums):
-// ranks within the workgroup from LDS, one global reservation per
-// workgroup and depth
-__global__ void __launch_bounds__(kB) k_scatter(GpuBvh g) {
-  __shared__ uint32_t s_cnt[kMaxTreeDepth], s_base[kMaxTreeDepth];
-  for (uint32_t d = threadIdx.x; d < kMaxTreeDepth; d += kB) s_cnt[d] = 0u;
-  __syncthreads();
-  const int m = (int)g.misc[7];
-  const int i = (int)(blockIdx.x * kB + threadIdx.x);
-  const bool live = i < m - 1;
-  const uint32_t d = live ? g.depth[i] : 0u;
-  const uint32_t rank = live ? atomicAdd(&s_cnt[d], 1u) : 0u;
-  __syncthreads();
-  for (uint32_t e = threadIdx.x; e < kMaxTreeDepth; e += kB)
-    s_base[e] = s_cnt[e] ? atomicAdd(g.level + kMaxTreeDepth + e, s_cnt[e]) : 0u;
-  __syncthreads();
-  if (live) g.order[s_base[d] + rank] = (uint32_t)i;
+  auto take = [&](uint64_t t) {
+    const float* b = g.box + 6 * (size_t)(t - 1);
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = fminf(lo[a], b[a]);
+      hi[a] = fmaxf(hi[a], b[3 + a]);
+    }
+  };
+  for (uint64_t l = (uint64_t)m + first, r = (uint64_t)m + last + 1u; l < r; l >>= 1, r >>= 1) {
+    if (l & 1u) take(l++);
+    if (r & 1u) take(--r);
+  }
 }
 
 // four-wide nodes sit at even binary depths; a subtree of at most max_leaf
 // triangles is a leaf and is not opened
-// (the per-depth counts are summed in LDS first: one global atomic per
-// workgroup and depth instead of one per node on a few dozen addresses)
-__global__ void __launch_bounds__(kB) k_heads(GpuBvh g) {
-  __shared__ uint32_t s_cnt[kMaxTreeDepth];
-  for (uint32_t d = threadIdx.x; d < kMaxTreeDepth; d += kB) s_cnt[d] = 0u;
-  __syncthreads();
+__global__ void __launch_bounds__(kBig) k_heads(GpuBvh g) {
+  __shared__ uint32_t buf[kBig / 64];
   const int m = (int)g.misc[7];
-  const int i = (int)(blockIdx.x * kB + threadIdx.x);
-  uint32_t is_head = 0;
-  if (i < m - 1) {
-    int depth = 0;
-    for (int n = g.parent[i]; n >= 0 && depth < (int)kMaxTreeDepth - 1; n = g.parent[n]) ++depth;
-    g.depth[i] = (uint32_t)depth;
-    atomicAdd(&s_cnt[depth], 1u);
-    const uint32_t count = g.range[2 * i + 1] - g.range[2 * i] + 1u;
-    is_head = (i == 0 || ((depth & 1) == 0 && count > g.max_leaf)) ? 1u : 0u;
-    atomicMax(g.misc + 11, (uint32_t)depth);
-    if (is_head) atomicMax(g.misc + 10, (uint32_t)depth / 2u);
+  uint32_t deepest = 0;
+  for (uint32_t i = blockIdx.x * kBig + threadIdx.x; i < g.nt; i += gridDim.x * kBig) {
+    uint32_t is_head = 0;
+    if ((int)i < m - 1) {
+      int depth = 0;
+      for (int n = g.parent[i]; n >= 0 && depth < (int)kMaxTreeDepth - 1; n = g.parent[n]) ++depth;
+      const uint32_t count = g.range[2 * i + 1] - g.range[2 * i] + 1u;
+      is_head = (i == 0 || ((depth & 1) == 0 && count > g.max_leaf)) ? 1u : 0u;
+      if (is_head) deepest = op_max(deepest, (uint32_t)depth / 2u);
+    }
+    g.flag[i] = is_head;
   }
-  if (i < (int)g.nt) g.flag[i] = is_head;
-  __syncthreads();
-  for (uint32_t d = threadIdx.x; d < kMaxTreeDepth; d += kB)
-    if (s_cnt[d]) atomicAdd(g.level + d, s_cnt[d]);
+  deepest = block_reduce(deepest, buf, op_max);
+  if (threadIdx.x == 0) atomicMax(g.misc + 10, deepest);
 }
 
+// node index of each head, and the head of each node
 __global__ void __launch_bounds__(kB) k_head_index(GpuBvh g, const uint32_t* scanned) {
   const int m = (int)g.misc[7];
   const int i = (int)(blockIdx.x * kB + threadIdx.x);
   if (i >= m - 1) return;
-  g.head[i] = g.flag[i] ? (int32_t)scanned[i] : -1;
-  if (i == m - 2) g.misc[8] = scanned[i] + g.flag[i];
+  const uint32_t node = scanned[i];
+  g.head[i] = g.flag[i] ? (int32_t)node : -1;
+  if (g.flag[i]) g.order[node] = (uint32_t)i;
+  if (i == m - 2) g.misc[8] = node + g.flag[i];
 }
 
 // the host build's node frame: origin at the low corner, the smallest power
-// of two step with the extent within 255 steps
+// of two step with the extent within 255 steps.  With ext = f 2^x, f in
+// [1/2, 1), that is 2^(x - 8) when f <= 255 / 256 and 2^(x - 7) otherwise.
 __device__ __forceinline__ void quantise_axis(float lo, float hi, float& origin, uint32_t& ebyte) {
   origin = lo;
   const double ext = (double)hi - (double)lo;
   int e = 0;  // a node with no box at all keeps step 1 (see the host build)
   if (ext > 0.0) {
-    frexp(ext / 255.0, &e);
-    while (e > -126 && ext <= 255.0 * ldexp(1.0, e - 1)) --e;
-    while (ext > 255.0 * ldexp(1.0, e)) ++e;
-    e = max(e, -126);
+    int x;
+    const double f = frexp(ext, &x);
+    e = max(f <= 255.0 / 256.0 ? x - 8 : x - 7, -126);
   }
   ebyte = (uint32_t)(e + 127);
 }
@@ -327,10 +400,13 @@ struct Kid {
   bool empty;
 };
 
-__device__ void write_node(Node4* out, const Kid* kids, int n_kids, float pad) {
+// (steps are powers of two, so dividing by one is an exact scaling)
+__device__ __forceinline__ void write_node(Node4* out, const Kid (&kids)[4], float pad) {
   float clo[4][3], chi[4][3];
   float nlo[3] = {INFINITY, INFINITY, INFINITY}, nhi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int j = 0; j < n_kids; ++j)
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
       clo[j][a] = kids[j].empty ? 0.0f : kids[j].lo[a] - pad;
       chi[j][a] = kids[j].empty ? 0.0f : kids[j].hi[a] + pad;
@@ -339,18 +415,21 @@ __device__ void write_node(Node4* out, const Kid* kids, int n_kids, float pad) {
         nhi[a] = fmaxf(nhi[a], chi[j][a]);
       }
     }
+#pragma unroll
   for (int a = 0; a < 3; ++a)
     if (!(nlo[a] <= nhi[a])) nlo[a] = nhi[a] = 0.0f;
   float origin[3];
   uint32_t eb[3];
+#pragma unroll
   for (int a = 0; a < 3; ++a) quantise_axis(nlo[a], nhi[a], origin[a], eb[a]);
   uint32_t qlo[3] = {0u, 0u, 0u}, qhi[3] = {0u, 0u, 0u};
-  int32_t ref[4] = {kEmpty, kEmpty, kEmpty, kEmpty};
-  for (int j = 0; j < n_kids; ++j) {
+  int32_t ref[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const double sc = ldexp(1.0, (int)eb[a] - 127);
-      const double lo = floor(((double)clo[j][a] - (double)origin[a]) / sc);
-      const double hi = ceil(((double)chi[j][a] - (double)origin[a]) / sc);
+      const double lo = floor(ldexp((double)clo[j][a] - (double)origin[a], 127 - (int)eb[a]));
+      const double hi = ceil(ldexp((double)chi[j][a] - (double)origin[a], 127 - (int)eb[a]));
       const uint32_t ql = (uint32_t)fmin(255.0, fmax(0.0, lo));
       const uint32_t qh = (uint32_t)fmin(255.0, fmax(0.0, hi));
       qlo[a] |= ql << (8 * j);
@@ -364,75 +443,66 @@ __device__ void write_node(Node4* out, const Kid* kids, int n_kids, float pad) {
   *out = nd;
 }
 
-__device__ __forceinline__ void kid_of(const GpuBvh& g, int m, int x, bool as_leaf, Kid& k) {
-  const uint32_t slot = (uint32_t)(x >= 0 ? x : (m - 1) + ~x);
-  const float* b = g.box + 6u * slot;
-  for (int a = 0; a < 3; ++a) {
-    k.lo[a] = b[a];
-    k.hi[a] = b[3 + a];
-  }
-  k.empty = false;
-  if (as_leaf) {
-    const uint32_t first = x >= 0 ? g.range[2 * x] : (uint32_t)~x;
-    const uint32_t last = x >= 0 ? g.range[2 * x + 1] : (uint32_t)~x;
-    k.ref = leaf_ref_encode(first, last - first + 1u);
-  } else {
-    k.ref = g.head[x];
-  }
-}
-
 __device__ __forceinline__ bool leaf_sized(const GpuBvh& g, int x) {
   return x < 0 || g.range[2 * x + 1] - g.range[2 * x] + 1u <= g.max_leaf;
+}
+
+// child x (an inner node, or ~position) of a four-wide node; none: an empty
+// slot.  Returns 1 for a leaf.
+__device__ __forceinline__ uint32_t kid_of(const GpuBvh& g, uint32_t m, bool none, int x, Kid& k) {
+  k.empty = none;
+  k.ref = kEmpty;
+  for (int a = 0; a < 3; ++a) k.lo[a] = k.hi[a] = 0.0f;
+  if (none) return 0u;
+  const uint32_t first = x >= 0 ? g.range[2 * x] : (uint32_t)~x;
+  const uint32_t last = x >= 0 ? g.range[2 * x + 1] : (uint32_t)~x;
+  const bool leaf = x < 0 || last - first + 1u <= g.max_leaf;
+  k.ref = leaf ? leaf_ref_encode(first, last - first + 1u) : g.head[x];
+  range_box(g, m, first, last, k.lo, k.hi);
+  return leaf ? 1u : 0u;
 }
 
 // one four-wide node per head: its two binary children, each opened into
 // its own two children unless it is a leaf
 __global__ void __launch_bounds__(kB) k_emit(GpuBvh g, Node4* nodes, bool count) {
-  const int m = (int)g.misc[7];
-  const int i = (int)(blockIdx.x * kB + threadIdx.x);
+  __shared__ uint32_t buf[kB / 64];
+  const uint32_t m = g.misc[7];
   const float pad = __uint_as_float(g.misc[6]) * (1.0f / 262144.0f);
+  uint32_t leaves = 0;
   if (m < 2) {
     // the root must be an inner node: at most one triangle hangs below it
-    if (i == 0) {
-      Kid k[2];
-      int n = 0;
-      if (m == 1) {
-        kid_of(g, m, ~0, true, k[0]);
-        n = 1;
-      }
-      write_node(nodes, k, n, pad);
-      if (count) g.misc[9] = (uint32_t)n;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      Kid k[4];
+      leaves = kid_of(g, m, m == 0, ~0, k[0]);
+      for (int j = 1; j < 4; ++j) kid_of(g, m, true, 0, k[j]);
+      write_node(nodes, k, pad);
     }
-    return;
-  }
-  if (i >= m - 1 || g.head[i] < 0) return;
-  Kid kids[4];
-  int n = 0;
-  uint32_t leaves = 0;
-  for (int s = 0; s < 2; ++s) {
-    const int x = g.child[2 * i + s];
-    if (leaf_sized(g, x)) {
-      kid_of(g, m, x, true, kids[n++]);
-      ++leaves;
-    } else {
-      for (int u = 0; u < 2; ++u) {
-        const int y = g.child[2 * x + u];
-        const bool lf = leaf_sized(g, y);
-        kid_of(g, m, y, lf, kids[n++]);
-        leaves += lf ? 1u : 0u;
-      }
+  } else {
+    const uint32_t n = g.misc[8];
+    for (uint32_t node = blockIdx.x * kB + threadIdx.x; node < n; node += gridDim.x * kB) {
+      const uint32_t i = g.order[node];
+      const int a = g.child[2 * i], b = g.child[2 * i + 1];
+      const bool la = leaf_sized(g, a), lb = leaf_sized(g, b);
+      const int a0 = la ? a : g.child[2 * a], a1 = la ? 0 : g.child[2 * a + 1];
+      const int b0 = lb ? b : g.child[2 * b], b1 = lb ? 0 : g.child[2 * b + 1];
+      // in order, without gaps
+      Kid k[4];
+      leaves += kid_of(g, m, false, a0, k[0]);
+      leaves += kid_of(g, m, false, la ? b0 : a1, k[1]);
+      leaves += kid_of(g, m, la && lb, la ? b1 : b0, k[2]);
+      leaves += kid_of(g, m, la || lb, b1, k[3]);
+      write_node(nodes + node, k, pad);
     }
   }
-  write_node(nodes + g.head[i], kids, n, pad);
-  if (count) atomicAdd(g.misc + 9, leaves);
-}
-
-__global__ void k_zero_u32(uint32_t* p, uint32_t n) {
-  const uint32_t i = blockIdx.x * kB + threadIdx.x;
-  if (i < n) p[i] = 0u;
+  if (count) {
+    leaves = block_reduce<kB>(leaves, buf, op_add);
+    if (threadIdx.x == 0) atomicAdd(g.misc + 9, leaves);
+  }
 }
 
 inline dim3 grid_for(uint32_t n) { return dim3(n ? (n + kB - 1) / kB : 1u); }
+// grid of kBig-lane blocks whose lanes take several items each
+inline dim3 grid_strided(uint32_t n) { return dim3(std::min(n ? (n + kBig - 1) / kBig : 1u, 512u)); }
 
 }  // namespace
 
@@ -445,10 +515,8 @@ hipError_t gpu_bvh_build(GpuBvh& g, Node4* nodes, float4* tris, float4* aux, hip
   } while (0)
   hipLaunchKernelGGL(k_init_misc, dim3(1), dim3(64), 0, st, g.misc, false);
   RR_GB(hipGetLastError());
-  hipLaunchKernelGGL(k_zero_u32, grid_for(2 * kMaxTreeDepth), dim3(kB), 0, st, g.level, 2 * kMaxTreeDepth);
-  RR_GB(hipGetLastError());
   float4* cen = reinterpret_cast<float4*>(g.box);  // scratch until the boxes are formed
-  hipLaunchKernelGGL(k_prep, grid_for(nt), dim3(kB), 0, st, g, aux, cen, true);
+  hipLaunchKernelGGL(k_prep, grid_strided(nt), dim3(kBig), 0, st, g, aux, cen);
   RR_GB(hipGetLastError());
   hipLaunchKernelGGL(k_morton, grid_for(nt), dim3(kB), 0, st, g, cen);
   RR_GB(hipGetLastError());
@@ -456,7 +524,7 @@ hipError_t gpu_bvh_build(GpuBvh& g, Node4* nodes, float4* tris, float4* aux, hip
   RR_GB(rocprim::radix_sort_pairs(g.temp, bytes, g.keys, g.keys + nt, g.ids, g.sorted, nt, 0u, 32u, st));
   hipLaunchKernelGGL(k_internal, grid_for(nt), dim3(kB), 0, st, g);
   RR_GB(hipGetLastError());
-  hipLaunchKernelGGL(k_heads, grid_for(nt), dim3(kB), 0, st, g);
+  hipLaunchKernelGGL(k_heads, grid_strided(nt), dim3(kBig), 0, st, g);
   RR_GB(hipGetLastError());
   // node index of each head: exclusive scan of the head flags into the
   // first half of the key array (free after the sort)
@@ -464,26 +532,13 @@ hipError_t gpu_bvh_build(GpuBvh& g, Node4* nodes, float4* tris, float4* aux, hip
   RR_GB(rocprim::exclusive_scan(g.temp, bytes, g.flag, g.keys, 0u, (size_t)nt, rocprim::plus<uint32_t>(), st));
   hipLaunchKernelGGL(k_head_index, grid_for(nt), dim3(kB), 0, st, g, g.keys);
   RR_GB(hipGetLastError());
-  // depth buckets: counts to the host, prefix sums back as scatter cursors
   uint32_t h[kMiscWords];
-  std::vector<uint32_t> cnt(kMaxTreeDepth), off(kMaxTreeDepth);
-  RR_GB(hipMemcpyAsync(h, g.misc, sizeof h, hipMemcpyDeviceToHost, st));
-  RR_GB(hipMemcpyAsync(cnt.data(), g.level, 4 * kMaxTreeDepth, hipMemcpyDeviceToHost, st));
-  RR_GB(hipStreamSynchronize(st));
-  uint32_t acc = 0;
-  for (uint32_t d = 0; d < kMaxTreeDepth; ++d) {
-    off[d] = acc;
-    acc += cnt[d];
-  }
-  RR_GB(hipMemcpyAsync(g.level + kMaxTreeDepth, off.data(), 4 * kMaxTreeDepth, hipMemcpyHostToDevice, st));
-  hipLaunchKernelGGL(k_scatter, grid_for(nt), dim3(kB), 0, st, g);
-  RR_GB(hipGetLastError());
-  g.level_cnt = cnt;
-  g.level_off = off;
-  RR_GB(gpu_bvh_refit(g, nodes, tris, aux, st, false));
   RR_GB(hipMemcpyAsync(h, g.misc, sizeof h, hipMemcpyDeviceToHost, st));
   RR_GB(hipStreamSynchronize(st));
   g.m = h[7];
+  RR_GB(gpu_bvh_refit(g, nodes, tris, aux, st, false));
+  RR_GB(hipMemcpyAsync(h, g.misc, sizeof h, hipMemcpyDeviceToHost, st));
+  RR_GB(hipStreamSynchronize(st));
   g.n_nodes = g.m >= 2 ? h[8] : 1u;
   g.n_leaves = h[9];
   g.max_depth = g.m >= 2 ? h[10] : 0u;
@@ -494,24 +549,26 @@ hipError_t gpu_bvh_build(GpuBvh& g, Node4* nodes, float4* tris, float4* aux, hip
   return hipSuccess;
 }
 
-hipError_t gpu_bvh_refit(GpuBvh& g, Node4* nodes, float4* tris, float4* aux, hipStream_t st, bool refit) {
-  const uint32_t nt = g.nt;
+hipError_t gpu_bvh_refit(const GpuBvh& g, Node4* nodes, float4* tris, float4* aux, hipStream_t st, bool refit) {
   hipError_t e;
   if (refit) {
     hipLaunchKernelGGL(k_init_misc, dim3(1), dim3(64), 0, st, g.misc, true);
     RR_GB(hipGetLastError());
-    hipLaunchKernelGGL(k_prep, grid_for(nt), dim3(kB), 0, st, g, aux, nullptr, false);
-    RR_GB(hipGetLastError());
+    hipLaunchKernelGGL(k_leaves<true>, grid_strided(g.nt), dim3(kBig), 0, st, g, tris, aux);
+  } else {
+    hipLaunchKernelGGL(k_leaves<false>, grid_strided(g.m), dim3(kBig), 0, st, g, tris, aux);
   }
-  hipLaunchKernelGGL(k_leaves, grid_for(nt), dim3(kB), 0, st, g, tris);
   RR_GB(hipGetLastError());
-  for (int d = (int)g.level_cnt.size() - 1; d >= 0; --d) {
-    const uint32_t c = g.level_cnt[(size_t)d];
-    if (!c) continue;
-    hipLaunchKernelGGL(k_box_level, grid_for(c), dim3(kB), 0, st, g, g.level_off[(size_t)d], c);
-    RR_GB(hipGetLastError());
+  if (g.m >= 2) {
+    // inner nodes 1 .. m - 1: levels floor(log2(m - 1)) .. 0, kSegLevels a launch
+    for (int deep = 31 - __builtin_clz(g.m - 1u); deep >= 0;) {
+      const int root = std::max(deep - kSegLevels + 1, 0);
+      hipLaunchKernelGGL(k_seg, dim3(1u << root), dim3(kB), 0, st, g, (uint32_t)root, (uint32_t)(deep - root + 1));
+      RR_GB(hipGetLastError());
+      deep = root - 1;
+    }
   }
-  hipLaunchKernelGGL(k_emit, grid_for(nt), dim3(kB), 0, st, g, nodes, !refit);
+  hipLaunchKernelGGL(k_emit, dim3(std::min(grid_for(refit ? g.n_nodes : g.m).x, 2048u)), dim3(kB), 0, st, g, nodes, !refit);
   RR_GB(hipGetLastError());
 #undef RR_GB
   return hipSuccess;
@@ -548,7 +605,6 @@ __global__ void __launch_bounds__(kB) k_hr_level(GpuBvh g, Node4* nodes, const f
   const Node4 nd = nodes[id];
   const int32_t refs[4] = {nd.w3.x, nd.w3.y, nd.w3.z, nd.w3.w};
   Kid kids[4];
-  const int n_kids = 4;
   float nlo[3] = {INFINITY, INFINITY, INFINITY}, nhi[3] = {-INFINITY, -INFINITY, -INFINITY};
   for (int j = 0; j < 4; ++j) {
     Kid& kd = kids[j];
@@ -591,7 +647,7 @@ __global__ void __launch_bounds__(kB) k_hr_level(GpuBvh g, Node4* nodes, const f
         nhi[a] = fmaxf(nhi[a], kd.hi[a]);
       }
   }
-  write_node(nodes + id, kids, n_kids, pad);
+  write_node(nodes + id, kids, pad);
   for (int a = 0; a < 3; ++a) {
     nbox[6u * id + (uint32_t)a] = nlo[a];
     nbox[6u * id + 3u + (uint32_t)a] = nhi[a];
@@ -649,7 +705,7 @@ hipError_t host_refit(HostRefit& r, const float* V, uint32_t nv, Node4* nodes, f
   hipError_t e;
   hipLaunchKernelGGL(k_init_misc, dim3(1), dim3(64), 0, st, r.misc, true);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_prep, grid_for(r.nt), dim3(kB), 0, st, g, aux, nullptr, false);
+  hipLaunchKernelGGL(k_normals, grid_strided(r.nt), dim3(kBig), 0, st, g, aux);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(k_hr_tris, grid_for(r.n_leaf_tris), dim3(kB), 0, st, g, tris, r.n_leaf_tris);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -686,7 +742,7 @@ hipError_t rocprim_sizes(size_t n, size_t* sort_bytes, size_t* scan_bytes) {
 
 void gpu_bvh_free(GpuBvh& g) {
   void* ptrs[] = {g.V, g.F, g.M, g.sorted, g.child, g.parent, g.range, g.head, g.box, g.flag, g.misc, g.temp,
-                  g.keys, g.ids, g.depth, g.order, g.level};
+                  g.keys, g.ids, g.order};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   g = GpuBvh();
