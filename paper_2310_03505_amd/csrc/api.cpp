@@ -540,6 +540,8 @@ rr_status make_post_args(rr_context* ctx, const rr_post_params* p, PostArgs& a) 
   a.pamp = p->perlin_amp;
   a.cell_az = p->perlin_amp > 0.0f ? p->perlin_cell_az : 1.0;
   a.cell_bins = p->perlin_amp > 0.0f ? p->perlin_cell_bins : 1.0;
+  a.rcell_az = 1.0 / a.cell_az;
+  a.rcell_bins = 1.0 / a.cell_bins;
   a.db_floor = p->db_floor;
   a.max_value = (double)p->max_value;
   a.px_scale = a.max_value / (0.0 - a.db_floor);

@@ -27,6 +27,7 @@ struct PostArgs {
   double w[2 * kPostMaxR + 1];  // blur weights, normalised to sum 1
   double uamp, pamp;            // uniform and gradient-noise amplitudes
   double cell_az, cell_bins;    // gradient-noise lattice spacing (>= 1)
+  double rcell_az, rcell_bins;  // their reciprocals
   double db_floor, max_value;
   double px_scale;              // max_value / (0 - db_floor)
   uint64_t seed;
@@ -34,10 +35,11 @@ struct PostArgs {
   uint32_t gcap;                // gradient-table rows per lattice column (0: no gradient noise)
 };
 
-// Dynamic LDS of one k_post workgroup: the gradient table (2 x gcap float2)
-// and, with a blur, the float64 tile of 1024 bins plus the halo.
+// Dynamic LDS of one k_post workgroup: the logarithm table (128 x 16 bytes),
+// the gradient table (2 x gcap x 16 bytes) and, with a blur, the float64 tile
+// of 1024 bins plus the halo.
 inline size_t post_lds_bytes(const PostArgs& a) {
-  return (size_t)2 * a.gcap * 8 + (a.R > 0 ? (size_t)(kPostTile + 2 * a.R) * 8 : 0);
+  return (size_t)128 * 16 + (size_t)2 * a.gcap * 16 + (a.R > 0 ? (size_t)(kPostTile + 2 * a.R) * 8 : 0);
 }
 
 hipError_t launch_post(const PostArgs& a, hipStream_t st);
