@@ -341,12 +341,19 @@ rr_status run(rr_context* ctx, const rr_scene* sc, std::vector<DevScan>& scans,
   DevMaterial* d_mats = reinterpret_cast<DevMaterial*>(ws + L.off_mats);
   uint32_t* d_ctr = reinterpret_cast<uint32_t*>(ws + L.off_ctr);
   auto* d_acc = reinterpret_cast<unsigned long long*>(ws + L.off_acc);
-  if (upload) {
+  bool masked = false;
+  for (const DevScan& q : scans) masked = masked || q.mask != nullptr;
+  // one scan's tables go with its first launch
+  const bool with_first = upload && scans.size() == 1 && !masked && tables_fit(n_mats);
+  std::vector<DevMaterial> first_mats;
+  if (with_first) {
+    scans[0].prim_base = 0;
+    scans[0].acc_base = 0;
+    make_materials(mats, n_mats, beam_width_for_mats, first_mats);
+  } else if (upload) {
     rr_status us = upload_tables(ctx, scans, ps, mats, n_mats, ws, st, beam_width_for_mats);
     if (us) return us;
   }
-  bool masked = false;
-  for (const DevScan& q : scans) masked = masked || q.mask != nullptr;
   if (L.air) {
     if (sc->bvh.width == 8) return fail(ctx, RR_EINVAL, "air-path returns need a four-wide BVH");
     if (ctx->fused) return fail(ctx, RR_EINVAL, "air-path returns need the level-by-level launches");
@@ -357,8 +364,9 @@ rr_status run(rr_context* ctx, const rr_scene* sc, std::vector<DevScan>& scans,
     if (scans[i].records && (uint64_t)scans[i].n_prim * stride > 0xffffffffull)
       return fail(ctx, RR_EINVAL, "records exceed 2^32 entries");
   }
-  // without masks every primary has a fixed queue slot and level 0 is full
-  HIP_TRY(ctx, launch_clear(d_acc, (size_t)L.acc_cells, d_ctr, masked ? 0u : (uint32_t)L.n_first, st));
+  // without masks every primary has a fixed queue slot and level 0 is full:
+  // the first launch clears the accumulator and the counters itself
+  if (masked) HIP_TRY(ctx, launch_clear(d_acc, (size_t)L.acc_cells, d_ctr, st));
   for (size_t i = 0; i < scans.size(); ++i)
     if (scans[i].records)
       HIP_TRY(ctx, launch_fill_i32(scans[i].records,
@@ -434,11 +442,11 @@ rr_status run(rr_context* ctx, const rr_scene* sc, std::vector<DevScan>& scans,
   rr_status rs;
   a.depth = 0;
   a.out = queue_at(ws, L, 0);
-  {
-    uint64_t blocks = (L.n_first + kBlock - 1) / kBlock;
-    uint32_t grid = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(blocks, 1), flat_cap);
-    if ((rs = timed_launch(0, 0, [&] { return launch_raygen(a, grid, st); }))) return rs;
-  }
+  if ((rs = timed_launch(0, 0, [&] {
+         return launch_raygen(a, (size_t)L.acc_cells, with_first ? scans.data() : nullptr, first_mats.data(), n_mats,
+                              flat_cap, st);
+       })))
+    return rs;
   uint64_t level_bound = L.n_first;
   if (ctx->fused) {
     // every level in one persistent launch; each wave keeps its rays' children

@@ -24,6 +24,10 @@
 // accuracy near the specular direction (lobe_pow).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cstring>
+#include <type_traits>
+
 #include "kernels.h"
 #include "philox.h"
 
@@ -990,35 +994,77 @@ __device__ __forceinline__ void put_ray(const QueueView& q, uint32_t slot, float
   q.m[slot] = meta;
 }
 
-// Primary rays of every scan (level 0).  Work items are global primary
-// indices; masked primaries are skipped; the rest are appended to queue 0.
-__global__ void __launch_bounds__(kBlock) k_raygen(LevelArgs A) {
+// Words passed as kernel arguments (at most 4 KB of them).
+struct Blob {
+  uint32_t n_words;
+  uint32_t w[760];
+};
+// The scan and material tables of one scan, with the arguments of its first
+// launch: the DevScan at word 0, the materials at word kMatsWord.
+constexpr uint32_t kMatsWord = 64;
+static_assert(sizeof(DevScan) <= 4 * kMatsWord, "table layout");
+struct NoTables {};
+
+// Primary `pid` of a scan; false if it is masked out.
+__device__ __forceinline__ bool first_ray(const DevScan& s, uint32_t pid, float& dx, float& dy, float& dz, float& g) {
+  if (s.mask && !s.mask[pid]) return false;
+  const uint32_t k = pid / s.n_s, i = pid - k * s.n_s;
+  gen_primary(s, k, i, dx, dy, dz, g);
+  return true;
+}
+
+// First launch of a scan: primary rays of every scan (level 0).  Work items
+// are global primary indices; masked primaries are skipped and the rest
+// appended to queue 0.  Without masks (kClear) primary gp sits at slot gp, so
+// nothing here depends on the counters and the launch also clears the
+// accumulator and the counters; with one scan (kInline) it also brings the
+// tables, in its arguments: one launch instead of four.  Bound by launches
+// where the scan is small: room scan (400 x 64 rays) 67.1 us with four
+// launches, 61.7 with one; 64 room scans in a graph 749 and 736 (clear and
+// rays at once); large scans within their spread.
+template <bool kClear, class Tables>
+__global__ void __launch_bounds__(kBlock) k_raygen(LevelArgs A, size_t n_acc, uint32_t* tables, uint32_t* mats, Tables T) {
+  constexpr bool kInline = std::is_same_v<Tables, Blob>;
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
-  for (uint32_t base = wave * 64u; base < A.n_first; base += n_waves * 64u) {
+  const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, n_tid = gridDim.x * blockDim.x;
+  if constexpr (kClear) {
+    for (size_t j = tid; j < n_acc; j += n_tid) A.acc[j] = 0ull;
+    if (tid < (uint32_t)kCtrWords) A.counters[tid] = tid == (uint32_t)kCtrCount ? A.n_first : 0u;
+  }
+  if constexpr (kInline) {
+    if (blockIdx.x == 0) {
+      for (uint32_t i = threadIdx.x; i < sizeof(DevScan) / 4; i += kBlock) tables[i] = T.w[i];
+      for (uint32_t i = kMatsWord + threadIdx.x; i < T.n_words; i += kBlock) mats[i - kMatsWord] = T.w[i];
+    }
+  }
+  for (uint32_t base = tid & ~63u; base < A.n_first; base += n_tid) {
     const uint32_t gp = base + lane;
     bool active = gp < A.n_first;
     uint32_t scan = 0, pid = 0;
     float dx = 1, dy = 0, dz = 0, g = 1, ox = 0, oy = 0, oz = 0;
     double E = 0.0;
     if (active) {
-      uint32_t lo = 0, hi = A.n_scans - 1;
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if (A.scans[mid].prim_base <= gp)
-          lo = mid;
-        else
-          hi = mid - 1;
-      }
-      scan = lo;
-      const DevScan& s = A.scans[scan];
-      pid = gp - s.prim_base;
-      if (s.mask && !s.mask[pid]) {
-        active = false;
+      if constexpr (kInline) {
+        const DevScan& s = *reinterpret_cast<const DevScan*>(T.w);
+        pid = gp;
+        active = first_ray(s, pid, dx, dy, dz, g);
+        ox = s.pos[0];
+        oy = s.pos[1];
+        oz = s.pos[2];
+        E = (double)s.e0;
       } else {
-        const uint32_t k = pid / s.n_s, i = pid - k * s.n_s;
-        gen_primary(s, k, i, dx, dy, dz, g);
+        uint32_t lo = 0, hi = A.n_scans - 1;
+        while (lo < hi) {
+          const uint32_t mid = (lo + hi + 1) >> 1;
+          if (A.scans[mid].prim_base <= gp)
+            lo = mid;
+          else
+            hi = mid - 1;
+        }
+        scan = lo;
+        const DevScan& s = A.scans[scan];
+        pid = gp - s.prim_base;
+        active = first_ray(s, pid, dx, dy, dz, g);
         ox = s.pos[0];
         oy = s.pos[1];
         oz = s.pos[2];
@@ -1026,7 +1072,7 @@ __global__ void __launch_bounds__(kBlock) k_raygen(LevelArgs A) {
       }
     }
     uint32_t slot = gp;  // no mask: primary gp sits at slot gp (count preset)
-    if (A.masked) {
+    if constexpr (!kClear) {
       uint64_t mask;
       slot = wave_append(active, A.counters + kCtrCount, lane, mask);
     }
@@ -1747,20 +1793,15 @@ __global__ void __launch_bounds__(kTraceBlock) k_scan(LevelArgs A) {
 }
 
 // ---------------------------------------------------------------- helpers
-struct Blob {
-  uint32_t n_words;
-  uint32_t w[760];
-};
-
 __global__ void k_put(uint32_t* dst, Blob b) {
   for (uint32_t i = threadIdx.x; i < b.n_words; i += blockDim.x) dst[i] = b.w[i];
 }
 
-__global__ void k_clear(unsigned long long* acc, size_t n_acc, uint32_t* counters, uint32_t count0) {
+__global__ void k_clear(unsigned long long* acc, size_t n_acc, uint32_t* counters) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   size_t stride = (size_t)gridDim.x * blockDim.x;
   for (size_t j = i; j < n_acc; j += stride) acc[j] = 0ull;
-  if (i < (size_t)kCtrWords) counters[i] = (i == (size_t)kCtrCount) ? count0 : 0u;
+  if (i < (size_t)kCtrWords) counters[i] = 0u;
 }
 
 // Random 64-byte gathers over a working set (a bandwidth probe with the
@@ -1819,12 +1860,11 @@ hipError_t put_blob(void* dst, const void* src, size_t bytes, hipStream_t st) {
   return hipSuccess;
 }
 
-hipError_t launch_clear(unsigned long long* acc, size_t n_acc, uint32_t* counters, uint32_t count0,
-                        hipStream_t st) {
+hipError_t launch_clear(unsigned long long* acc, size_t n_acc, uint32_t* counters, hipStream_t st) {
   size_t blocks = (n_acc + 255) / 256;
   if (blocks < (size_t)(kCtrWords + 255) / 256) blocks = (size_t)(kCtrWords + 255) / 256;
   if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, st, acc, n_acc, counters, count0);
+  hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, st, acc, n_acc, counters);
   return hipGetLastError();
 }
 
@@ -1836,8 +1876,26 @@ hipError_t launch_fill_i32(int32_t* p, size_t n, int32_t v, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_raygen(const LevelArgs& a, uint32_t grid, hipStream_t st) {
-  hipLaunchKernelGGL(k_raygen, dim3(grid ? grid : 1), dim3(kBlock), 0, st, a);
+bool tables_fit(size_t n_mats) { return 4 * (size_t)kMatsWord + sizeof(DevMaterial) * n_mats <= sizeof(Blob::w); }
+
+hipError_t launch_raygen(const LevelArgs& a, size_t n_acc, const DevScan* scan, const DevMaterial* mats, size_t n_mats,
+                         uint32_t max_blocks, hipStream_t st) {
+  // four accumulator cells per lane: at least a block per 1,024 cells
+  const size_t items = a.masked ? a.n_first : std::max<size_t>(a.n_first, std::max<size_t>(n_acc / 4, kCtrWords));
+  const uint32_t grid = (uint32_t)std::min<size_t>(std::max<size_t>((items + kBlock - 1) / kBlock, 1), max_blocks);
+  uint32_t* const ds = reinterpret_cast<uint32_t*>(const_cast<DevScan*>(a.scans));
+  uint32_t* const dm = reinterpret_cast<uint32_t*>(const_cast<DevMaterial*>(a.mats));
+  if (scan) {
+    Blob t;
+    t.n_words = kMatsWord + (uint32_t)(sizeof(DevMaterial) * n_mats / 4);
+    std::memcpy(t.w, scan, sizeof *scan);
+    std::memcpy(t.w + kMatsWord, mats, sizeof(DevMaterial) * n_mats);
+    hipLaunchKernelGGL((k_raygen<true, Blob>), dim3(grid), dim3(kBlock), 0, st, a, n_acc, ds, dm, t);
+  } else if (!a.masked) {
+    hipLaunchKernelGGL((k_raygen<true, NoTables>), dim3(grid), dim3(kBlock), 0, st, a, n_acc, ds, dm, NoTables{});
+  } else {
+    hipLaunchKernelGGL((k_raygen<false, NoTables>), dim3(grid), dim3(kBlock), 0, st, a, n_acc, ds, dm, NoTables{});
+  }
   return hipGetLastError();
 }
 
