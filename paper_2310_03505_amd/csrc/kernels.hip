@@ -312,21 +312,27 @@ __device__ __forceinline__ void normalize3(float& x, float& y, float& z) {
 // owner's (t, id) minimum, and they cull against that minimum.  The owner
 // finishes once no helper walks for it.  The result is the same minimum, so
 // images and records do not change.  Held to 80 registers, as the plain
-// variant, so that both keep 24 waves per CU resident.
+// variant, and to 12,800 bytes of LDS a block, so that both keep 24 waves per
+// CU resident: LDS is handed out in steps of 1,280 bytes, and with 12,928
+// only 22 waves fit (urban block 1.284 ms, city at 400 x 200 0.510, with 24
+// 1.225 and 0.477).
+constexpr uint32_t kTraceLds = (kStack + 1) * kTraceBlock * 4 + kTraceBlock / 64 * kLeafRing * 5 + kTraceBlock * 12;
+static_assert(160 * 1024 / ((kTraceLds + 1279) / 1280 * 1280) * (kTraceBlock / 64) >= 24, "24 waves per CU");
 template <bool kCount, bool kShadow, bool kHelp>
 __global__ void __launch_bounds__(kTraceBlock) __attribute__((amdgpu_waves_per_eu(6)))
 k_trace(LevelArgs A) {
-  // row 0 of the stack is never written: the top of an empty stack reads it
+  // row 0 of the stack holds no entries: the top of an empty stack reads it;
+  // a wave's part of it also holds the victim lane of each helper rank
   __shared__ int32_t lds_stack[(kStack + 1) * kTraceBlock];
   __shared__ uint32_t lds_leaf[kTraceBlock / 64][kLeafRing];     // leaf reference
   __shared__ uint8_t lds_own[kTraceBlock / 64][kLeafRing];       // lane that appended it
   __shared__ unsigned long long lds_best[kTraceBlock];           // (t bits << 32) | original id
   __shared__ uint32_t lds_help[kHelp ? kTraceBlock : 1];          // helpers walking for each lane's ray
-  __shared__ uint8_t lds_pair[kHelp ? kTraceBlock / 64 : 1][64];  // victim lane of each helper rank
   int32_t* stk = lds_stack + kTraceBlock + threadIdx.x;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wib = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // wave-uniform
   const uint32_t wave_base = wib * 64u;
+  int32_t* const pair = lds_stack + wave_base;
   const uint32_t n_in = kShadow ? min(A.counters[kCtrShadow], A.shq_cap) : min(A.counters[kCtrCount + A.depth], A.cap);
   const Node4* __restrict__ nodes = A.nodes;
   const float4* __restrict__ tris = A.tris;
@@ -676,11 +682,11 @@ k_trace(LevelArgs A) {
       if (k) {
         const uint32_t rv = lane_prefix(give_m), ri = lane_prefix(idle_m);
         const bool victim = __builtin_amdgcn_inverse_ballot_w64(give_m) && rv < k;
-        if (victim) lds_pair[wib][rv] = (uint8_t)lane;
+        if (victim) pair[rv] = (int32_t)lane;
         __builtin_amdgcn_wave_barrier();
         const uint64_t takes_m = idle_m & __ballot(ri < k);
         const bool takes = __builtin_amdgcn_inverse_ballot_w64(takes_m);
-        const int v = takes ? (int)lds_pair[wib][ri] : (int)lane;
+        const int v = takes ? pair[ri] : (int)lane;
         const int vsb = (int)lane_value((uint32_t)sb, v);
         const uint32_t vown = lane_value(owner, v);
         const float rox = lane_value(ox, v), roy = lane_value(oy, v), roz = lane_value(oz, v);
