@@ -462,14 +462,14 @@ rr_status run(rr_context* ctx, const rr_scene* sc, std::vector<DevScan>& scans,
     const uint32_t tgrid = trace_blocks(level_bound, trace_grid);
     const bool help = tail_help_on(ctx, level_bound, tgrid);
     if ((rs = timed_launch(1, d, [&] { return launch_trace(a, tgrid, help, st); }))) return rs;
-    // shade grid: 32 x 512 lanes per CU (the air-path variant 24 x 256): many
+    // shade grid: 32 x 768 lanes per CU (the air-path variant 24 x 256): many
     // short blocks, so a finishing block hands its CU to the next while the
     // other resident blocks still run
-    const uint32_t sb = (uint32_t)shade_block(a.air);
-    const uint32_t lanes_per_cu = a.air ? 24u * 256u : 32u * 512u;
+    const uint32_t sb = (uint32_t)shade_block(a.air, level_bound, (uint32_t)ctx->n_cu);
+    const uint32_t lanes_per_cu = a.air ? 24u * 256u : 32u * 768u;
     uint64_t sblocks = (level_bound + sb - 1) / sb;
     uint32_t sgrid = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(sblocks, 1), (uint64_t)ctx->n_cu * (lanes_per_cu / sb));
-    if ((rs = timed_launch(2, d, [&] { return launch_shade(a, sgrid, st); }))) return rs;
+    if ((rs = timed_launch(2, d, [&] { return launch_shade(a, sgrid, (int)sb, st); }))) return rs;
     level_bound = std::min<uint64_t>(level_bound * 2, L.cap);
   }
   if (L.air && L.max_b > 1) {

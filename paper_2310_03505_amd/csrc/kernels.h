@@ -74,7 +74,8 @@ hipError_t launch_raygen(const LevelArgs& a, size_t n_acc, const DevScan* scan, 
                          uint32_t max_blocks, hipStream_t st);
 bool tables_fit(size_t n_mats);
 hipError_t launch_trace(const LevelArgs& a, uint32_t grid, bool help, hipStream_t st);
-hipError_t launch_shade(const LevelArgs& a, uint32_t grid, hipStream_t st);
+// lanes: shade_block's
+hipError_t launch_shade(const LevelArgs& a, uint32_t grid, int lanes, hipStream_t st);
 // Visibility of the sensor for the air-path returns of every level (the
 // closest-hit traversal bounded by each ray's distance to the sensor); the
 // unblocked returns are added to the accumulator.  a.depth must be 0.
@@ -96,11 +97,27 @@ constexpr int kProfMaxVisits = kProfTailActive + 8;
 constexpr int kProfPoolMax = kProfMaxVisits + 8;  // fused scan: largest child pool of a wave
 constexpr int kProfWords = kProfPoolMax + 1;
 constexpr int kBlock = 256;
-// shade: lanes per block (one queue reservation per block step); the air-path
-// variant holds twice the registers and keeps two blocks per CU with 256
-constexpr int kShadeBlock = 512;
+// shade: lanes per block (one queue reservation per block step).  Every block
+// clears and flushes a table of accumulator cells, so large blocks are better
+// where a level fills the card with them twice over, small ones where it has
+// at most one ray per lane of a 256-lane block per CU and would leave CUs
+// idle.  256 / 512 / 768 lanes throughout: 64 room scans (1.6 million rays
+// and more a level) 816 / 737 / 732 us, urban block (400 x 1024) 1287 / 1228
+// / 1212, one room scan (25,600 rays) 60.8 / 61.5 / 63.7; 256 lanes up to
+// 131,000 rays and 768 above slow the city at 400 x 200 (levels of 80,000 to
+// 500,000) from 477 to 483, the rule below does not.  The air-path variant
+// holds twice the registers: 256 lanes, three blocks per CU (384: 1421 ->
+// 1586 us for the urban block).
+constexpr int kShadeBlock = 768;
+constexpr int kShadeBlockMedium = 512;
+constexpr int kShadeBlockSmall = 256;
 constexpr int kShadeBlockAir = 256;
-constexpr int shade_block(bool air) { return air ? kShadeBlockAir : kShadeBlock; }
+inline int shade_block(bool air, uint64_t rays, uint32_t n_cu) {
+  return air                             ? kShadeBlockAir
+         : rays <= (uint64_t)n_cu * 256u  ? kShadeBlockSmall
+         : rays <= (uint64_t)n_cu * 1536u ? kShadeBlockMedium
+                                          : kShadeBlock;
+}
 constexpr uint32_t kMaxLevels = 8;   // bounce levels (interactions per path) at most
 constexpr uint32_t kLeafRing = 256;  // four-wide trace: leaf entries per wave (power of two)
 // a node step appends up to four leaves per lane and runs only while they fit

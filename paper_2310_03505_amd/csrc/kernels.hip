@@ -1332,13 +1332,13 @@ __device__ __forceinline__ void shade_hit(const LevelArgs& A, const float4 a, co
 // BRDF, range binning (Sec. III-B) and the two children.
 // Register budgets for occupancy: the kernel mostly waits on its loads, and
 // more resident waves hide more of that wait.  The closest-hit form keeps to
-// 80 registers, six waves per SIMD (three 512-lane blocks per CU instead of
-// two); the air-path form to 168, three waves per SIMD (three 256-lane blocks
-// instead of two).  The closest-hit form spills one register to scratch.
-template <bool kCount, bool kAirPath>
-__global__ void __launch_bounds__(shade_block(kAirPath)) __attribute__((amdgpu_waves_per_eu(kAirPath ? 3 : 6)))
+// 80 registers, six waves per SIMD; the air-path form to 168, three waves per
+// SIMD (three 256-lane blocks instead of two).  The closest-hit form spills
+// one register to scratch.  (The hit id loaded one step ahead, so that the
+// normal's load need not wait for it, changed nothing.)
+template <bool kCount, bool kAirPath, int kShadeLanes>
+__global__ void __launch_bounds__(kShadeLanes) __attribute__((amdgpu_waves_per_eu(kAirPath ? 3 : 6)))
 k_shade(LevelArgs A) {
-  constexpr int kShadeLanes = shade_block(kAirPath);
   // returns of the block's rays are summed in an LDS hash table keyed by
   // accumulator cell and flushed with one global atomic per cell at the end;
   // the block works on a contiguous range of the level, whose rays mostly
@@ -1942,20 +1942,21 @@ hipError_t launch_scan(const LevelArgs& a, uint32_t grid, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_shade(const LevelArgs& a, uint32_t grid, hipStream_t st) {
-  const dim3 g(grid ? grid : 1), b(shade_block(a.air));
-  if (a.air) {
-    if (a.prof)
-      hipLaunchKernelGGL((k_shade<true, true>), g, b, 0, st, a);
-    else
-      hipLaunchKernelGGL((k_shade<false, true>), g, b, 0, st, a);
-  } else {
-    if (a.prof)
-      hipLaunchKernelGGL((k_shade<true, false>), g, b, 0, st, a);
-    else
-      hipLaunchKernelGGL((k_shade<false, false>), g, b, 0, st, a);
-  }
+template <bool kAirPath, int kLanes>
+static hipError_t shade_with(const LevelArgs& a, uint32_t grid, hipStream_t st) {
+  const dim3 g(grid ? grid : 1), b(kLanes);
+  if (a.prof)
+    hipLaunchKernelGGL((k_shade<true, kAirPath, kLanes>), g, b, 0, st, a);
+  else
+    hipLaunchKernelGGL((k_shade<false, kAirPath, kLanes>), g, b, 0, st, a);
   return hipGetLastError();
+}
+
+hipError_t launch_shade(const LevelArgs& a, uint32_t grid, int lanes, hipStream_t st) {
+  if (a.air) return shade_with<true, kShadeBlockAir>(a, grid, st);
+  if (lanes == kShadeBlockSmall) return shade_with<false, kShadeBlockSmall>(a, grid, st);
+  if (lanes == kShadeBlockMedium) return shade_with<false, kShadeBlockMedium>(a, grid, st);
+  return shade_with<false, kShadeBlock>(a, grid, st);
 }
 
 hipError_t launch_finalize(const DevScan* scans, uint32_t n_scans, const unsigned long long* acc,

@@ -64,3 +64,29 @@ def test_first_launch_forms_agree(R, n_mats, n_az, rays, bins):
     finally:
         sc.release()
         ctx.close()
+
+
+@pytest.mark.parametrize("n_az", [256, 1536])
+@pytest.mark.parametrize("more", [0, 1])
+def test_shade_block_sizes_agree(R, n_az, more):
+    """Levels at and just above the sizes where the interaction's blocks grow
+    (256 and 1,536 rays per compute unit): the scan alone and as one of a
+    batch that runs the largest blocks gives the same image bit for bit, with
+    the same rays."""
+    import torch
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    s = W.tiny_room(n_azimuth=n_az, rays_per_beam=n_cu + more, beam_width_deg=20.0, max_bounces=3)
+    ctx = R.Context(0)
+    sc = R.Scene(ctx, s.vertices, s.indices, s.tri_material)
+    try:
+        alone, st = R.rr_radar_scan(ctx.handle, sc.handle, s.pose, s.params, s.materials, stats=True)
+        n = -(-4 * 1536 // n_az)
+        images, bst = R.rr_radar_scan_batch(ctx.handle, sc.handle, [(s.pose, s.params)] * n, s.materials, stats=True)
+        torch.cuda.synchronize()
+        assert st["overflow"] == 0 and bst["overflow"] == 0
+        assert all(torch.equal(i, alone) for i in images)
+        assert bst["rays_per_depth"] == [n * r for r in st["rays_per_depth"]]
+        assert float(alone.max()) > 0
+    finally:
+        sc.release()
+        ctx.close()
