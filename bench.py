@@ -48,6 +48,8 @@ N_CU = 256
 # the same figure as the L2's 8 XCDs x 16 channels x 128 B per clock.
 VMEM_PEAK_GBS = N_CU * 64 * CLOCK_GHZ
 # VALU issue: one wave64 instruction per SIMD every 4 clocks, 4 SIMDs per CU
+# (a yardstick, not a ceiling: additions, FMAs and logic issue on either of a
+# SIMD's two vector pipes, about one per 2.8 clocks measured)
 VALU_ISSUE_PEAK = N_CU * 4 * CLOCK_GHZ * 1e9 / 4.0   # wave64 instructions/s
 FP32_PEAK_TFLOPS = 78.6   # 256 CU x 64 lanes x 2.4 GHz x 2 (non-packed FMA)
 
@@ -61,11 +63,11 @@ FP32_PEAK_TFLOPS = 78.6   # 256 CU x 64 lanes x 2.4 GHz x 2 (non-packed FMA)
 # FETCH_SIZE counts half the bytes a copy reads, WRITE_SIZE all it writes.
 # The figures hold only for the kernel sources they were taken on.
 TRACE_COUNTERS = {
-    "large_scene_2m": dict(fetch_kib=357690.6, write_kib=164837.6, sq_insts_valu=899413801.4,
-                           grbm_gui_active_per_xcd=28479774.6 / 8, tcp_accesses=804344143.0,
-                           tcp_tcc_read_req=64219566.5),
+    "large_scene_2m": dict(fetch_kib=340669.0, write_kib=168470.9, sq_insts_valu=781074541.2,
+                           grbm_gui_active_per_xcd=24040217.5 / 8, tcp_accesses=849183494.7,
+                           tcp_tcc_read_req=62633862.0),
 }
-TRACE_COUNTERS_SOURCES = "a25686804ea058ca7c81a68fa78081718f81839e270492e25fbcffb41d851115"
+TRACE_COUNTERS_SOURCES = "ddda21fa1bce608d512ba7857be7f36622b57c3f02ca882817ed945389cc1d2b"
 COUNTER_SCALE = dict(fetch_scale=2.0, write_scale=1.0)
 TRACE_SOURCES = ("kernels.hip", "kernels.h", "rr_internal.h", "bvh.cpp", "api_internal.h", "api.cpp")
 

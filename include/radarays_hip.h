@@ -266,8 +266,8 @@ rr_status rr_bvh_get_info(const rr_scene* scene, rr_bvh_info* out);
  * bytes per triangle and 28 per node), later ones allocate nothing.  Triangles that were degenerate at
  * build time stay out of the tree; child boxes of split references grow to
  * whole triangles, so a tree built with spatial or early splits loses their
- * tightness and keeps their extra references (urban block: 2.06 ms per scan
- * after a refit back to the built vertices, 1.83 before): build trees meant
+ * tightness and keeps their extra references (urban block: 1.53 ms per scan
+ * after a refit back to the built vertices, 1.34 before): build trees meant
  * for refitting with spatial_pct = -1.  The host copy of the mesh is not
  * changed, so
  * rr_bvh_build afterwards builds from the uploaded vertices.  ESTATE

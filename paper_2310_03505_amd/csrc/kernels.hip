@@ -5,15 +5,16 @@
 //             (Sec. III-A, Eq. 2), appended to ray queue 0;
 //   k_trace   (per bounce level) closest hit of every queued ray through the
 //             BVH: persistent lanes that take a new ray as soon as theirs is
-//             done (rays claimed 64 at a time from per-segment cursors), up
-//             to kNodeSteps node steps between two scheduling decisions,
+//             done (a first share of the queue per wave, the rest claimed 64
+//             rays at a time from per-segment cursors), up to kNodeSteps node
+//             steps between two scheduling decisions,
 //             leaf tests batched wave-wide, and on levels with few rays per
 //             lane idle lanes helping the wave's unfinished rays;
 //   k_shade   (per bounce level) the interaction at each hit (Snell,
 //             Fresnel, standard BRDF return, Sec. III-A), the return binned
 //             into the polar image with a 64-bit fixed-point atomic
 //             (Sec. III-B), and up to two children appended to the next queue
-//             (one reservation per 512-lane block step);
+//             (one reservation per block step);
 //   k_scan    the optional one-launch form of k_trace + k_shade over every
 //             level, each wave keeping its own rays' children.
 //
@@ -265,8 +266,7 @@ __device__ __forceinline__ void normalize3(float& x, float& y, float& z) {
 // Closest-hit traversal, persistent and replenishing (after Aila & Laine,
 // "Understanding the efficiency of ray traversal on GPUs", HPG 2009): every
 // lane owns one ray at a time; lanes whose ray has finished take new rays
-// (claim_rays, one atomic per wave and claim) as soon as A.refill lanes are
-// idle.
+// (the wave's share, then claim_rays) as soon as A.refill lanes are idle.
 //
 // Each loop iteration is either a node step or a triangle phase, decided for
 // the whole wave.  In a node step every tracing lane visits one inner node:
