@@ -32,7 +32,8 @@ struct GpuBvh {
   uint32_t* misc = nullptr;    // scalars (bounds, counts), see bvh_gpu.hip
   void* temp = nullptr;        // sort / scan scratch
   size_t temp_bytes = 0;
-  uint32_t* keys = nullptr;    // [2][nt] Morton keys (sort in / out)
+  uint32_t* keys = nullptr;    // [2][nt] Morton keys (sort in / out); after a build [nodes][2], the first and
+                               // last sorted position under each four-wide node (k_emit)
   uint32_t* ids = nullptr;     // [nt] sort values in
   uint32_t n_nodes = 0, n_leaves = 0, max_depth = 0, max_stack = 0;
   float pad = 0.0f;
