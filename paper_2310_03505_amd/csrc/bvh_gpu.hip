@@ -493,10 +493,10 @@ __global__ void __launch_bounds__(kB) k_emit(GpuBvh g, Node4* nodes) {
         uint2 r[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          if (ref[j] < 0)
+          if (ref[j] < 0)  // (kEmpty too: its range is not used)
             r[j] = make_uint2(leaf_start(ref[j]), leaf_start(ref[j]) + leaf_count(ref[j]) - 1u);
           else
-            r[j] = span[ref[j] == kEmpty ? 0 : ref[j]];
+            r[j] = span[ref[j]];
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -700,7 +700,7 @@ hipError_t host_refit_setup(HostRefit& r, const Node4* nodes, uint32_t n_nodes, 
   for (uint32_t i = 0; i < n_nodes; ++i) {
     const int32_t refs[4] = {nodes[i].w3.x, nodes[i].w3.y, nodes[i].w3.z, nodes[i].w3.w};
     for (int j = 0; j < 4; ++j) {
-      if (refs[j] == kEmpty || refs[j] < 0) continue;
+      if (refs[j] < 0) continue;
       if ((uint32_t)refs[j] >= n_nodes || (uint32_t)refs[j] <= i) return hipErrorInvalidValue;
       depth[(uint32_t)refs[j]] = depth[i] + 1u;
       max_d = std::max(max_d, depth[i] + 1u);

@@ -55,22 +55,10 @@ __device__ __forceinline__ double min_f64(double a, double b) {
   return r;
 }
 
-// Three-input logic operations, one instruction each, which issues at the
-// rate of additions (twice that of selects, shifts and v_and_or / v_or3):
-// b where the bits of m are set and a elsewhere; a | b | c; (a & b) | c.
+// b where the bits of m are set and a elsewhere, as or3
 __device__ __forceinline__ uint32_t select_bits(uint32_t a, uint32_t b, uint32_t m) {
   uint32_t r;
   asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xd8" : "=v"(r) : "v"(a), "v"(b), "v"(m));
-  return r;
-}
-__device__ __forceinline__ uint32_t or3(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t r;
-  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xfe" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t r;
-  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xea" : "=v"(r) : "v"(a), "s"(b), "v"(c));
   return r;
 }
 
@@ -468,12 +456,13 @@ k_trace(LevelArgs A) {
       const uint32_t n = min(queued, 64u);
       const bool take = lane < n;
       const uint32_t pos = (ring_tail + lane) & (kLeafRing - 1u);
-      const uint32_t ref = take ? lds_leaf[wib][pos] : 0u;
+      const uint32_t ref = take ? lds_leaf[wib][pos] : (uint32_t)kEmpty;
       const int own = take ? (int)lds_own[wib][pos] : (int)lane;
       const float rox = lane_value(ox, own), roy = lane_value(oy, own), roz = lane_value(oz, own);
       const float rdx = lane_value(dx, own), rdy = lane_value(dy, own), rdz = lane_value(dz, own);
       const uint32_t rexcl = lane_value(excl, own);
-      if (take) {
+      // (kEmpty: no entry, or an empty slot that was met, see node4_child)
+      if ((int32_t)ref != kEmpty) {
         unsigned long long cb = lds_best[wave_base + own];
         float tmax = __uint_as_float((uint32_t)(cb >> 32));
         const uint32_t start = leaf_start((int32_t)ref), count = leaf_count((int32_t)ref);
@@ -527,7 +516,8 @@ k_trace(LevelArgs A) {
         // Every lane runs the node step; one without a node to visit (idle or
         // done) reads the tree's last node and pushes and appends nothing.
         // A reference outside the tree (kEmpty: none) takes the next stack
-        // entry; `top`, the last entry in LDS, was read at the end of the
+        // entry, always an inner child (node4_child keeps empty slots off the
+        // stack); `top`, the last entry in LDS, was read at the end of the
         // step before.
         const uint64_t need = walk & __ballot((uint32_t)cur >= A.n_nodes);
         const uint64_t pop = need & __ballot(sp > sb);
@@ -551,24 +541,18 @@ k_trace(LevelArgs A) {
         }
         float tn[4], tf[4];
         node4_slabs(w0, w1, w2, ox, oy, oz, ix, iy, iz, sg, tn, tf);
-        // The hit tests are differences whose sign bits are combined with
-        // logic operations: subtraction and logic issue at twice the rate of
-        // compares and selects.  A lane that visits nothing has a negative
-        // limit.  Sort keys: the entry distance above the child reference as
-        // one float64, which orders as the distance does (both are >= 0);
-        // children not hit and leaves (references with the sign bit set) get
-        // the sign bit.  Far to near in five compare-exchanges of one minimum
-        // and one maximum each.
+        // The inner children met are sorted far to near in five
+        // compare-exchanges of one minimum and one maximum each.  A lane that
+        // visits nothing has a negative limit.
         const float tlim = __builtin_amdgcn_inverse_ballot_w64(vis) ? limit : -1.0f;
         const int32_t lref[4] = {w3.x, w3.y, w3.z, w3.w};
         uint64_t leaf[4];
         double key[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const uint32_t r = (uint32_t)lref[j];
-          const uint32_t m1 = __float_as_uint(fmaf(tf[j], kSlabSlack, -tn[j])), m2 = __float_as_uint(tlim - tn[j]);
-          leaf[j] = __ballot((int32_t)(r & ~(m1 | m2)) < 0);
-          key[j] = __hiloint2double((int)and_or(or3(m1, m2, r), 0x80000000u, __float_as_uint(tn[j])), lref[j]);
+          const ChildTest c = node4_child(lref[j], tn[j], tf[j], tlim);
+          leaf[j] = __ballot((int32_t)c.leaf < 0);
+          key[j] = __hiloint2double((int)c.key, lref[j]);
         }
 #define RR_CX(i, j)                            \
   {                                            \

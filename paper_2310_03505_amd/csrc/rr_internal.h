@@ -32,22 +32,26 @@ constexpr int kSpill = 80;     // further entries per lane in workspace memory
 //   w0 = (origin.x, origin.y, origin.z, step.x)
 //   w1 = (qlo.x[4], qlo.x[4] ^ qhi.x[4], qlo.y[4], qlo.y[4] ^ qhi.y[4])   one byte per child
 //   w2 = (qlo.z[4], qlo.z[4] ^ qhi.z[4], step.y, step.z)
-//   w3 = child refs: inner node index (< 2^30), kEmpty for no child, or a
-//        leaf: bit 31 | (count - 1) << 27 | first leaf triangle (< 2^27)
+//   w3 = child refs: inner node index (< 2^30), a leaf: bit 31 | (count - 1)
+//        << 27 | first leaf triangle (< 2^27), or kEmpty for no child
 // step: a power of two per axis, as a float (bits in w2).  Child j covers
 // origin + q * step on each axis, rounded outward from the padded float box,
 // so decoding never shrinks a box.  The xor form gives the planes on the
 // ray's near and far side with three logic operations per axis (which issue
 // at twice the rate of selects), and steps stored as floats need no decoding.  A slot without a
-// child (ref kEmpty) holds the inverted box qlo = 255, qhi = 0 on every
-// axis, which no ray interval meets (node4_slabs relies on it).
+// child (ref kEmpty) holds the inverted box qlo = 255, qhi = 0 on every axis.
+// A ray meets it only from so far away that 255 steps of the node's frame are
+// within the relative slack of the box test (kSlabSlack); kEmpty therefore
+// has the leaf bit, which keeps it off the stack, and no leaf can have its
+// value (sixteen triangles from 2^27 - 1 on).
 struct alignas(64) Node4 {
   float4 w0;
   uint4 w1, w2;
   int4 w3;
 };
 static_assert(sizeof(Node4) == 64, "node layout");
-constexpr int32_t kEmpty = 0x7fffffff;
+constexpr int32_t kEmpty = -1;
+static_assert(kEmpty < 0, "an empty slot must not become a stack entry");
 constexpr uint32_t kMaxLeafTris = 1u << 27;
 RR_HD int32_t leaf_ref_encode(uint32_t start, uint32_t count) {
   return (int32_t)(0x80000000u | ((count - 1u) << 27) | start);
@@ -244,7 +248,8 @@ RR_HD RaySigns ray_signs(const RayBox& r) {
 // otherwise; fma(q, s, b) is monotone in q, so choosing the byte planes by the
 // sign of 1/d equals taking min / max of both decoded bounds.  An empty slot
 // holds an inverted box (see Node4), whose entry distance exceeds its exit
-// distance by at least 255 quantisation steps.
+// distance by at least 255 quantisation steps: less than the slack of a
+// distance 2^20 times as long.
 RR_HD float max3_from0(float a, float b, float c) {
 #if defined(__HIP_DEVICE_COMPILE__)
   float r;
@@ -273,6 +278,46 @@ RR_HD void node4_slabs(const float4& w0, const uint4& w1, const uint4& w2, float
     tn[j] = max3_from0(tnx, tny, tnz);
     tf[j] = fminf(fminf(tfx, tfy), tfz);
   }
+}
+
+// a | b | c and (a & b) | c, b wave-uniform: one instruction each, which
+// issues at the rate of additions (twice that of selects, shifts and v_and_or
+// / v_or3).
+RR_HD uint32_t or3(uint32_t a, uint32_t b, uint32_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  uint32_t r;
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xfe" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+#else
+  return a | b | c;
+#endif
+}
+RR_HD uint32_t and_or(uint32_t a, uint32_t b, uint32_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  uint32_t r;
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xea" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+  return r;
+#else
+  return (a & b) | c;
+#endif
+}
+
+// One child of a node as k_trace takes it, from node4_slabs' distances and
+// the ray's limit with the slack (negative: nothing is met).  The hit tests
+// are differences whose sign bits are combined with logic operations:
+// subtraction and logic issue at twice the rate of compares and selects.
+// key: the high word of a float64 whose low word is the reference.  An inner
+// child that is met has its entry distance there, so that the float64 orders
+// as the distance does (both are >= 0); any other slot has the sign bit set.
+// leaf: the sign bit is set for a leaf that is met, and for an empty slot
+// whose box is (kEmpty), which has no triangles to test.
+struct ChildTest {
+  uint32_t leaf, key;
+};
+RR_HD ChildTest node4_child(int32_t ref, float tn, float tf, float tlim) {
+  const uint32_t r = (uint32_t)ref;
+  const uint32_t m1 = float_bits(fmaf(tf, kSlabSlack, -tn)), m2 = float_bits(tlim - tn);
+  return ChildTest{r & ~(m1 | m2), and_or(or3(m1, m2, r), 0x80000000u, float_bits(tn))};
 }
 
 // Power of two that takes a ray's largest distance tmax below 1/2.  With 1/d
