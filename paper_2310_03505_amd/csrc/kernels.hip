@@ -984,20 +984,24 @@ __device__ __forceinline__ void put_ray(const QueueView& q, uint32_t slot, float
   q.m[slot] = meta;
 }
 
-// Words passed as kernel arguments (at most 4 KB of them).
-struct Blob {
-  uint32_t n_words;
-  uint32_t w[760];
+// The tables of one scan, passed with the arguments of its first launch.
+struct FirstTables {
+  DevScan scan;
+  uint32_t n_mats;
+  DevMaterial mats[58];
 };
-// The scan and material tables of one scan, with the arguments of its first
-// launch: the DevScan at word 0, the materials at word kMatsWord.
-constexpr uint32_t kMatsWord = 64;
-static_assert(sizeof(DevScan) <= 4 * kMatsWord, "table layout");
+static_assert(offsetof(FirstTables, scan) % alignof(DevScan) == 0 &&
+                  offsetof(FirstTables, mats) % alignof(DevMaterial) == 0 && alignof(FirstTables) >= alignof(DevScan),
+              "read in place");
+static_assert(sizeof(LevelArgs) + sizeof(size_t) + 2 * sizeof(void*) + sizeof(FirstTables) <= 4096,
+              "the arguments of a launch take at most 4 KB");
+static_assert(sizeof(DevScan) % 4 == 0 && sizeof(DevMaterial) % 4 == 0, "copied by words");
 struct NoTables {};
 
-// Primary `pid` of a scan; false if it is masked out.
+// Primary `pid` of a scan; false if it is masked out (kMasks: it may be).
+template <bool kMasks>
 __device__ __forceinline__ bool first_ray(const DevScan& s, uint32_t pid, float& dx, float& dy, float& dz, float& g) {
-  if (s.mask && !s.mask[pid]) return false;
+  if (kMasks && s.mask && !s.mask[pid]) return false;
   const uint32_t k = pid / s.n_s, i = pid - k * s.n_s;
   gen_primary(s, k, i, dx, dy, dz, g);
   return true;
@@ -1013,8 +1017,9 @@ __device__ __forceinline__ bool first_ray(const DevScan& s, uint32_t pid, float&
 // launches, 61.7 with one; 64 room scans in a graph 749 and 736 (clear and
 // rays at once); large scans within their spread.
 template <bool kClear, class Tables>
-__global__ void __launch_bounds__(kBlock) k_raygen(LevelArgs A, size_t n_acc, uint32_t* tables, uint32_t* mats, Tables T) {
-  constexpr bool kInline = std::is_same_v<Tables, Blob>;
+__global__ void __launch_bounds__(kBlock) k_raygen(LevelArgs A, size_t n_acc, uint32_t* scan_out, uint32_t* mats_out,
+                                                  Tables T) {
+  constexpr bool kInline = std::is_same_v<Tables, FirstTables>;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, n_tid = gridDim.x * blockDim.x;
   if constexpr (kClear) {
@@ -1023,8 +1028,12 @@ __global__ void __launch_bounds__(kBlock) k_raygen(LevelArgs A, size_t n_acc, ui
   }
   if constexpr (kInline) {
     if (blockIdx.x == 0) {
-      for (uint32_t i = threadIdx.x; i < sizeof(DevScan) / 4; i += kBlock) tables[i] = T.w[i];
-      for (uint32_t i = kMatsWord + threadIdx.x; i < T.n_words; i += kBlock) mats[i - kMatsWord] = T.w[i];
+      const auto copy = [](uint32_t* dst, const void* src, uint32_t words) {
+        for (uint32_t i = threadIdx.x; i < words; i += kBlock)
+          __builtin_memcpy(dst + i, static_cast<const char*>(src) + 4u * i, 4);
+      };
+      copy(scan_out, &T.scan, sizeof(DevScan) / 4);
+      copy(mats_out, T.mats, T.n_mats * (uint32_t)(sizeof(DevMaterial) / 4));
     }
   }
   for (uint32_t base = tid & ~63u; base < A.n_first; base += n_tid) {
@@ -1035,9 +1044,13 @@ __global__ void __launch_bounds__(kBlock) k_raygen(LevelArgs A, size_t n_acc, ui
     double E = 0.0;
     if (active) {
       if constexpr (kInline) {
-        const DevScan& s = *reinterpret_cast<const DevScan*>(T.w);
+        // (the offset, always 0, keeps the scan's words from being read ahead
+        // of the loop, where 63 of them are spilled)
+        uint32_t zero;
+        asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+        const DevScan& s = (&T.scan)[zero];
         pid = gp;
-        active = first_ray(s, pid, dx, dy, dz, g);
+        active = first_ray<!kClear>(s, pid, dx, dy, dz, g);
         ox = s.pos[0];
         oy = s.pos[1];
         oz = s.pos[2];
@@ -1054,7 +1067,7 @@ __global__ void __launch_bounds__(kBlock) k_raygen(LevelArgs A, size_t n_acc, ui
         scan = lo;
         const DevScan& s = A.scans[scan];
         pid = gp - s.prim_base;
-        active = first_ray(s, pid, dx, dy, dz, g);
+        active = first_ray<!kClear>(s, pid, dx, dy, dz, g);
         ox = s.pos[0];
         oy = s.pos[1];
         oz = s.pos[2];
@@ -1783,6 +1796,12 @@ __global__ void __launch_bounds__(kTraceBlock) k_scan(LevelArgs A) {
 }
 
 // ---------------------------------------------------------------- helpers
+// Words passed as kernel arguments (at most 4 KB of them).
+struct Blob {
+  uint32_t n_words;
+  uint32_t w[760];
+};
+
 __global__ void k_put(uint32_t* dst, Blob b) {
   for (uint32_t i = threadIdx.x; i < b.n_words; i += blockDim.x) dst[i] = b.w[i];
 }
@@ -1866,7 +1885,7 @@ hipError_t launch_fill_i32(int32_t* p, size_t n, int32_t v, hipStream_t st) {
   return hipGetLastError();
 }
 
-bool tables_fit(size_t n_mats) { return 4 * (size_t)kMatsWord + sizeof(DevMaterial) * n_mats <= sizeof(Blob::w); }
+bool tables_fit(size_t n_mats) { return sizeof(DevMaterial) * n_mats <= sizeof(FirstTables::mats); }
 
 hipError_t launch_raygen(const LevelArgs& a, size_t n_acc, const DevScan* scan, const DevMaterial* mats, size_t n_mats,
                          uint32_t max_blocks, hipStream_t st) {
@@ -1876,11 +1895,11 @@ hipError_t launch_raygen(const LevelArgs& a, size_t n_acc, const DevScan* scan, 
   uint32_t* const ds = reinterpret_cast<uint32_t*>(const_cast<DevScan*>(a.scans));
   uint32_t* const dm = reinterpret_cast<uint32_t*>(const_cast<DevMaterial*>(a.mats));
   if (scan) {
-    Blob t;
-    t.n_words = kMatsWord + (uint32_t)(sizeof(DevMaterial) * n_mats / 4);
-    std::memcpy(t.w, scan, sizeof *scan);
-    std::memcpy(t.w + kMatsWord, mats, sizeof(DevMaterial) * n_mats);
-    hipLaunchKernelGGL((k_raygen<true, Blob>), dim3(grid), dim3(kBlock), 0, st, a, n_acc, ds, dm, t);
+    FirstTables t;
+    t.scan = *scan;
+    t.n_mats = (uint32_t)n_mats;
+    std::copy(mats, mats + n_mats, t.mats);
+    hipLaunchKernelGGL((k_raygen<true, FirstTables>), dim3(grid), dim3(kBlock), 0, st, a, n_acc, ds, dm, t);
   } else if (!a.masked) {
     hipLaunchKernelGGL((k_raygen<true, NoTables>), dim3(grid), dim3(kBlock), 0, st, a, n_acc, ds, dm, NoTables{});
   } else {
