@@ -271,22 +271,6 @@ uint32_t trace_grid_blocks(const rr_context* ctx) {
   return std::min(g, kSpillLanes / (uint32_t)kTraceBlock);
 }
 
-// Blocks of a trace launch over at most `bound` rays.  A launch of more rays
-// than the persistent grid has lanes fills that grid.  A smaller one is as
-// long as its longest walks, so its rays are spread over more waves than they
-// need: fewer rays per wave wait for each other, and the idle lanes help with
-// their walks from the start.  One wave per SIMD (1,024) down to eight rays
-// a wave, then 32 rays a wave; measured per pass against 64 / 32 / 16 / 8
-// rays a wave: 100 x 64 rays in the city, two levels (with the refit of that
-// frame) 1020 / 939 / 897 / 875 us; 400 x 64 in the room, three levels
-// 68.9 / 67.8 / 71.4 / 75.9; 400 x 200 in the city, four levels
-// 527 / 514 / 524 / 527.
-uint32_t trace_blocks(uint64_t bound, uint32_t grid_blocks) {
-  constexpr uint64_t kWaves = kTraceBlock / 64u;
-  const uint64_t waves = std::max<uint64_t>(std::min<uint64_t>((bound + 7) / 8, 1024u), (bound + 31) / 32);
-  return (uint32_t)std::min<uint64_t>(std::max<uint64_t>((waves + kWaves - 1) / kWaves, 1), grid_blocks);
-}
-
 // Tail helping (idle lanes walk subtrees of their wave's unfinished rays)
 // for a traversal launch whose rays number at most ctx->tail_help per lane
 // of its grid (`bound` is the launch's ray bound).  Few rays per lane leave
@@ -452,14 +436,14 @@ rr_status run(rr_context* ctx, const rr_scene* sc, std::vector<DevScan>& scans,
     // every level in one persistent launch; each wave keeps its rays' children
     a.depth = 0;
     a.in = queue_at(ws, L, 0);
-    const uint32_t tgrid = trace_blocks(L.n_first, trace_grid);
+    const uint32_t tgrid = trace_blocks(L.n_first, trace_grid, (uint32_t)ctx->n_cu);
     if ((rs = timed_launch(1, 0, [&] { return launch_scan(a, tgrid, st); }))) return rs;
   }
   for (uint32_t d = 0; d < (ctx->fused ? 0u : L.max_b); ++d) {
     a.depth = d;
     a.in = queue_at(ws, L, d & 1);
     a.out = queue_at(ws, L, (d + 1) & 1);
-    const uint32_t tgrid = trace_blocks(level_bound, trace_grid);
+    const uint32_t tgrid = trace_blocks(level_bound, trace_grid, (uint32_t)ctx->n_cu);
     const bool help = tail_help_on(ctx, level_bound, tgrid);
     if ((rs = timed_launch(1, d, [&] { return launch_trace(a, tgrid, help, st); }))) return rs;
     // shade grid: 32 x 768 lanes per CU (the air-path variant 24 x 256): many

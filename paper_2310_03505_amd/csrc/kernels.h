@@ -126,5 +126,23 @@ constexpr uint32_t kNodeSteps = 6;   // four-wide trace: node steps per refill/t
 constexpr uint32_t kLeafRing8 = 1024;  // eight-wide trace: leaf entries per wave (power of two)
 constexpr int kStack8 = 6;              // eight-wide trace: node groups per lane in LDS
 constexpr int kTraceBlock = 128;  // trace workgroup (LDS stack of kStack words per lane)
+// Blocks of a trace launch over at most `bound` rays, of a persistent grid of
+// grid_blocks.  A launch of more rays than that grid has lanes fills it.  A
+// smaller one is as long as its longest walks, so its rays are spread over
+// more waves than they need: fewer rays per wave wait for each other, and the
+// idle lanes help with their walks from the start.  One wave per SIMD (four a
+// compute unit) down to eight rays a wave, then 32 rays a wave; measured on
+// 256 units per pass against 64 / 32 / 16 / 8 rays a wave: 100 x 64 rays in
+// the city, two levels (with the refit of that frame) 1020 / 939 / 897 / 875
+// us; 400 x 64 in the room, three levels 68.9 / 67.8 / 71.4 / 75.9; 400 x 200
+// in the city, four levels 527 / 514 / 524 / 527.
+inline uint32_t trace_blocks(uint64_t bound, uint32_t grid_blocks, uint32_t n_cu) {
+  constexpr uint64_t kWaves = kTraceBlock / 64;
+  const uint64_t spread = (bound + 7) / 8, simds = 4u * (uint64_t)n_cu, packed = (bound + 31) / 32;
+  uint64_t waves = spread < simds ? spread : simds;
+  if (waves < packed) waves = packed;
+  const uint64_t blocks = (waves + kWaves - 1) / kWaves;
+  return blocks < 1 ? 1u : blocks < grid_blocks ? (uint32_t)blocks : grid_blocks;
+}
 
 }  // namespace rr
