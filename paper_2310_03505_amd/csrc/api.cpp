@@ -436,15 +436,17 @@ rr_status run(rr_context* ctx, const rr_scene* sc, std::vector<DevScan>& scans,
     // every level in one persistent launch; each wave keeps its rays' children
     a.depth = 0;
     a.in = queue_at(ws, L, 0);
-    const uint32_t tgrid = trace_blocks(L.n_first, trace_grid, (uint32_t)ctx->n_cu);
+    const uint32_t tgrid = trace_blocks(L.n_first, trace_grid, (uint32_t)ctx->n_cu, kSpreadRays);
     if ((rs = timed_launch(1, 0, [&] { return launch_scan(a, tgrid, st); }))) return rs;
   }
   for (uint32_t d = 0; d < (ctx->fused ? 0u : L.max_b); ++d) {
     a.depth = d;
     a.in = queue_at(ws, L, d & 1);
     a.out = queue_at(ws, L, (d + 1) & 1);
-    const uint32_t tgrid = trace_blocks(level_bound, trace_grid, (uint32_t)ctx->n_cu);
-    const bool help = tail_help_on(ctx, level_bound, tgrid);
+    uint32_t tgrid = trace_blocks(level_bound, trace_grid, (uint32_t)ctx->n_cu, kSpreadRays);
+    const bool help = sc->bvh.width != 8 && tail_help_on(ctx, level_bound, tgrid);
+    // without helpers a second wave per SIMD needs rays for every lane
+    if (!help) tgrid = trace_blocks(level_bound, trace_grid, (uint32_t)ctx->n_cu, kPackedRays);
     if ((rs = timed_launch(1, d, [&] { return launch_trace(a, tgrid, help, st); }))) return rs;
     // shade grid: 32 x 768 lanes per CU (the air-path variant 24 x 256): many
     // short blocks, so a finishing block hands its CU to the next while the

@@ -131,14 +131,23 @@ constexpr int kTraceBlock = 128;  // trace workgroup (LDS stack of kStack words 
 // smaller one is as long as its longest walks, so its rays are spread over
 // more waves than they need: fewer rays per wave wait for each other, and the
 // idle lanes help with their walks from the start.  One wave per SIMD (four a
-// compute unit) down to eight rays a wave, then 32 rays a wave; measured on
-// 256 units per pass against 64 / 32 / 16 / 8 rays a wave: 100 x 64 rays in
-// the city, two levels (with the refit of that frame) 1020 / 939 / 897 / 875
-// us; 400 x 64 in the room, three levels 68.9 / 67.8 / 71.4 / 75.9; 400 x 200
-// in the city, four levels 527 / 514 / 524 / 527.
-inline uint32_t trace_blocks(uint64_t bound, uint32_t grid_blocks, uint32_t n_cu) {
+// compute unit) down to eight rays a wave, then rays_per_wave.  Measured per
+// pass on 256 units with helpers against 64 / 32 / 16 / 8 rays a wave: 100 x
+// 64 rays in the city, two levels (with the refit of that frame) 1020 / 939 /
+// 897 / 875 us; 400 x 64 in the room, three levels 68.9 / 67.8 / 71.4 / 75.9;
+// 400 x 200 in the city, four levels 527 / 514 / 524 / 527: 32.  The one-launch
+// form, whose waves keep the children of their rays, gains most (32 against
+// 64: city 400 x 200 571 and 932 us, urban block 400 x 256 666 and 906).
+// Without helpers (tail helping off, the eight-wide tree) idle lanes do
+// nothing from one wave per SIMD on, and 64 is better (32 / 64: city 400 x 200
+// 340 / 326 and eight-wide 525 / 483, 400 x 64 259 / 244 and 382 / 357, urban
+// block 400 x 256 392 / 378 and 561 / 525), but one wave per SIMD still is
+// (against 64 rays a wave throughout: city 100 x 64 101 / 118 and 140 / 159).
+constexpr uint32_t kSpreadRays = 32, kPackedRays = 64;
+inline uint32_t trace_blocks(uint64_t bound, uint32_t grid_blocks, uint32_t n_cu, uint32_t rays_per_wave) {
   constexpr uint64_t kWaves = kTraceBlock / 64;
-  const uint64_t spread = (bound + 7) / 8, simds = 4u * (uint64_t)n_cu, packed = (bound + 31) / 32;
+  const uint64_t spread = (bound + 7) / 8, simds = 4u * (uint64_t)n_cu;
+  const uint64_t packed = (bound + rays_per_wave - 1) / rays_per_wave;
   uint64_t waves = spread < simds ? spread : simds;
   if (waves < packed) waves = packed;
   const uint64_t blocks = (waves + kWaves - 1) / kWaves;

@@ -10,8 +10,10 @@ PROGRAM = r"""
 #include <cstdlib>
 #include "kernels.h"
 int main(int argc, char** argv) {
-  for (int i = 1; i + 2 < argc; i += 3)
-    printf("%u\n", rr::trace_blocks(strtoull(argv[i], nullptr, 10), (uint32_t)atoi(argv[i + 1]), (uint32_t)atoi(argv[i + 2])));
+  for (int i = 1; i + 3 < argc; i += 4)
+    printf("%u\n", rr::trace_blocks(strtoull(argv[i], nullptr, 10), (uint32_t)atoi(argv[i + 1]),
+                                    (uint32_t)atoi(argv[i + 2]),
+                                    atoi(argv[i + 3]) ? rr::kSpreadRays : rr::kPackedRays));
   return 0;
 }
 """
@@ -35,18 +37,21 @@ def blocks(tmp_path_factory):
     return run
 
 
+@pytest.mark.parametrize("spread", [1, 0])
 @pytest.mark.parametrize("n_cu", [1, 32, 64, 128, 256, 304])
-def test_trace_blocks_scale_with_the_compute_units(blocks, n_cu):
+def test_trace_blocks_scale_with_the_compute_units(blocks, n_cu, spread):
     """A level is spread over at most one wave per SIMD, four of them a
-    compute unit, unless it has more than 32 rays for each; every ray has a
-    lane until the grid is full; the grid is never exceeded."""
+    compute unit, unless it has more than 32 rays for each, or 64 where idle
+    lanes cannot help; every ray has a lane until the grid is full; the grid
+    is never exceeded."""
+    rays = 32 if spread else 64
     grid = 24 * n_cu // WAVES
     bounds = [0, 1, 7, 8, 9, 31 * n_cu, 32 * n_cu, 32 * n_cu + 1, 128 * n_cu - 1, 128 * n_cu, 128 * n_cu + 1,
-              1000 * n_cu, 64 * 24 * n_cu, 10**9, 2**31]
-    for bound, got in zip(bounds, blocks([(b, grid, n_cu) for b in bounds])):
+              256 * n_cu, 256 * n_cu + 1, 1000 * n_cu, 64 * 24 * n_cu, 10**9, 2**31]
+    for bound, got in zip(bounds, blocks([(b, grid, n_cu, spread) for b in bounds])):
         assert 1 <= got <= max(grid, 1)
-        waves = max(min(-(-bound // 8), 4 * n_cu), -(-bound // 32))
+        waves = max(min(-(-bound // 8), 4 * n_cu), -(-bound // rays))
         assert got == min(max(-(-waves // WAVES), 1), grid)
         assert got == grid or got * WAVES * 64 >= bound
-        if bound <= 128 * n_cu:
+        if bound <= 4 * rays * n_cu:
             assert got * WAVES <= 4 * n_cu
