@@ -12,8 +12,12 @@
 // takes 4.5 clocks of a SIMD, so a pixel's instructions take longer than its
 // nine bytes of HBM traffic), hence fused multiply-adds, the blur's taps read
 // two at a time, divisions by the lattice spacing as multiplications with a
-// correction, and a logarithm by table.  64 images of 400 x 3776 with every
-// term on: 0.700 -> 0.459 ms (1.24 -> 1.90 TB/s); HBM alone would take 0.18.
+// correction, a logarithm by table, and nothing in scratch memory.  64 images
+// of 400 x 3776 with every term on: 0.700 -> 0.436 ms (1.24 -> 2.00 TB/s); HBM
+// alone would take 0.18.  The gradient table takes 16 bytes a lattice point:
+// with a lattice of one bin and a blur a block holds 44 KB of LDS, three blocks
+// per CU, and is still ahead of the plain form it replaced (1.69 -> 1.64 ms at
+// sigma 2; 0.96 -> 0.68 with a lattice of four bins).
 #include <hip/hip_runtime.h>
 
 #include "philox.h"
@@ -220,8 +224,13 @@ __global__ __launch_bounds__(kPostBlock) void k_post(PostArgs a) {
   const float h = halo_in ? hv : 0.0f;
   const int hslot = has_halo ? ((int)tid < R ? (int)tid : R + (int)nb + (int)tid - R) : -1;
 
-  LogEntry le;
-  if (tid < 128u) le = kLogTable[tid];
+  // (as one struct the entry would go through scratch memory: 454 -> 431 us
+  // for the 64 images)
+  double log_v = 0.0, log_l = 0.0;
+  if (tid < 128u) {
+    log_v = kLogTable[tid].v;
+    log_l = kLogTable[tid].l;
+  }
 
   // 2. gradient noise: lattice columns i0, i0 + 1 and rows jlo..jhi of this
   //    tile, computed while the loads are in flight
@@ -247,7 +256,7 @@ __global__ __launch_bounds__(kPostBlock) void k_post(PostArgs a) {
     }
   }
 
-  if (tid < 128u) logs[tid] = le;
+  if (tid < 128u) logs[tid] = LogEntry{log_v, log_l};
 
   // 3. the scan's float image, and the blur's LDS tile with its halo
   if constexpr (kFromAcc) {
