@@ -47,10 +47,13 @@ N_CU = 256
 # texture-data path returns 64 B per clock, so 256 CUs x 64 B x 2.4 GHz;
 # the same figure as the L2's 8 XCDs x 16 channels x 128 B per clock.
 VMEM_PEAK_GBS = N_CU * 64 * CLOCK_GHZ
-# VALU issue: one wave64 instruction per SIMD every 4 clocks, 4 SIMDs per CU
-# (a yardstick, not a ceiling: additions, FMAs and logic issue on either of a
-# SIMD's two vector pipes, about one per 2.8 clocks measured)
-VALU_ISSUE_PEAK = N_CU * 4 * CLOCK_GHZ * 1e9 / 4.0   # wave64 instructions/s
+# VALU issue, 4 SIMDs per CU: the highest rate measured, one wave64 instruction
+# per SIMD every 2.5 clocks, with FMAs and maxima interleaved.  Additions, FMAs
+# and logic issue on either of a SIMD's two vector pipes (2.6 to 2.9 clocks
+# alone), compares, selects, minima, shifts and conversions on one of them
+# (4.2 to 4.7 clocks alone).
+VALU_ISSUE_CLOCKS = 2.5
+VALU_ISSUE_PEAK = N_CU * 4 * CLOCK_GHZ * 1e9 / VALU_ISSUE_CLOCKS   # wave64 instructions/s
 FP32_PEAK_TFLOPS = 78.6   # 256 CU x 64 lanes x 2.4 GHz x 2 (non-packed FMA)
 
 # Counters of one k_trace dispatch, averaged over the trace dispatches of
@@ -63,11 +66,11 @@ FP32_PEAK_TFLOPS = 78.6   # 256 CU x 64 lanes x 2.4 GHz x 2 (non-packed FMA)
 # FETCH_SIZE counts half the bytes a copy reads, WRITE_SIZE all it writes.
 # The figures hold only for the kernel sources they were taken on.
 TRACE_COUNTERS = {
-    "large_scene_2m": dict(fetch_kib=340669.0, write_kib=168470.9, sq_insts_valu=781074541.2,
-                           grbm_gui_active_per_xcd=24040217.5 / 8, tcp_accesses=849183494.7,
-                           tcp_tcc_read_req=62633862.0),
+    "large_scene_2m": dict(fetch_kib=337360.8, write_kib=169670.6, sq_insts_valu=781718617.2,
+                           grbm_gui_active_per_xcd=24074296.9 / 8, tcp_accesses=849177833.3,
+                           tcp_tcc_read_req=62624837.9),
 }
-TRACE_COUNTERS_SOURCES = "ddda21fa1bce608d512ba7857be7f36622b57c3f02ca882817ed945389cc1d2b"
+TRACE_COUNTERS_SOURCES = "b85309d55ead45b3ead100c788882507e86b99728f66af92c4b32b400fb80f0e"
 COUNTER_SCALE = dict(fetch_scale=2.0, write_scale=1.0)
 TRACE_SOURCES = ("kernels.hip", "kernels.h", "rr_internal.h", "bvh.cpp", "api_internal.h", "api.cpp")
 
@@ -118,7 +121,7 @@ def cpu_model() -> str:
 
 def host_threads():
     """Threads for the oracle: every core of this process's affinity set,
-    capped at 16 (the GPU machine gives one GPU's jobs 16 host cores)."""
+    capped at 16 (one GPU's share of an eight-GPU machine's host cores)."""
     try:
         aff = len(os.sched_getaffinity(0))
     except AttributeError:
@@ -157,7 +160,7 @@ def cpu_baseline(scene, n_cols: int, per_col: int, full_segments: int):
                 scans_per_s_extrapolated=rate / max(full_segments, 1),
                 extrapolation="full scan = the scan's exact segment count / the sampled segment rate",
                 cpu_model=cpu_model(), nproc=os.cpu_count(), affinity_cores=aff,
-                thread_cap="16, the host cores the GPU box gives one GPU's jobs")
+                thread_cap="16, one GPU's share of an eight-GPU machine's host cores")
 
 
 def measure_scan(R, ctx, scene, sc, steps, warmup, roofline=True):
@@ -250,7 +253,7 @@ def roofline_of(res, wname, p):
                         insts_per_launch=None if ctr is None else ctr["sq_insts_valu"],
                         peak_insts_per_s=VALU_ISSUE_PEAK,
                         measured_clock_ghz=clock,
-                        source="SQ_INSTS_VALU x 4 clocks / (1024 SIMDs x 2.4 GHz x launch time)"),
+                        source="SQ_INSTS_VALU x 2.5 clocks / (1024 SIMDs x 2.4 GHz x launch time)"),
         vector_l1=l1,
         alu_fp32=dict(achieved_tflops=round(tfl, 3), peak_tflops=FP32_PEAK_TFLOPS,
                       frac=round(tfl / FP32_PEAK_TFLOPS, 4), flops_per_launch=int(flops_launch)),

@@ -2,7 +2,8 @@
 //
 // Host work per scan: validate, derive the per-scan constants (rotation,
 // Eq. 2 radius scale, beam-window coefficients of the standard BRDF), lay
-// out the workspace, and enqueue: clear -> bounce level 0..B-1 -> finalize,
+// out the workspace, and enqueue: rays (with the clear) -> bounce level
+// 0..B-1 -> finalize,
 // all on the caller's stream with no host synchronisation.
 #include <hip/hip_runtime.h>
 

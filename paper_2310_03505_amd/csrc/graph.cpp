@@ -1,8 +1,9 @@
 // graph.cpp -- captured launch sequences (rr_graph_*) and the launch
 // parameter autotuner (rr_autotune).
 //
-// A graph holds the whole per-batch sequence: clear, ray generation, one
-// trace and one shade launch per bounce level, finalize.  The scan and
+// A graph holds the whole per-batch sequence: ray generation (which clears,
+// unless a scan has a primary mask: then a clear before it), one trace and one
+// shade launch per bounce level, finalize.  The scan and
 // material tables are the only inputs that change between replays; they are
 // uploaded by a small kernel on the caller's stream right before the graph
 // is launched there, so the captured nodes never change.

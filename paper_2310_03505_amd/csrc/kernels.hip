@@ -281,7 +281,9 @@ __device__ __forceinline__ void normalize3(float& x, float& y, float& z) {
 // near sort is ten float64 minima and maxima, and a triangle's three loads
 // go out together, the next triangle's before this one is tested.  City scan
 // (400 x 4096 rays) 7.99 -> 6.90 ms, urban block (400 x 1024) 1.433 -> 1.295,
-// city at 400 x 200 0.607 -> 0.525.  Tried here and not kept: nodes loaded
+// city at 400 x 200 0.607 -> 0.525 (one pose each, both forms in turn on one
+// card; over poses and cards the city scan varies from 6.4 to 7.5 ms, the
+// ratio hardly).  Tried here and not kept: nodes loaded
 // by four lanes together through LDS (fewer L1 lines, but 4 KB of LDS per
 // wave leave 16 waves per CU: 7.86 against 7.02 ms) or by two lanes with a
 // register exchange (6.93 against 6.94), seven waves per SIMD (72 registers,
